@@ -3,6 +3,7 @@
 // the method; every step runs in the HIP kernels.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdarg>
 #include <cstddef>
 #include <cstdio>
@@ -56,6 +57,13 @@ mpmi_status ok(mpmi_ctx ctx) {
 mpmi_status check_hip(mpmi_ctx ctx, hipError_t e, const char* what) {
   if (e == hipSuccess) return ok(ctx);
   return fail(ctx, MPMI_EDEVICE, "%s: %s", what, hipGetErrorString(e));
+}
+
+// The condition estimate of a fit: the square root of the ratio of the scaled
+// Gram matrix's extreme eigenvalues; infinite when they give none.
+double condition(const mpmi::FitInfo& info) {
+  const double c = info.lmax * info.lmin_inv;
+  return c > 0.0 ? std::sqrt(c) : INFINITY;
 }
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -322,11 +330,10 @@ mpmi_status koopman_fit(mpmi_ctx ctx, const mpmi_system* sys, const double* X, c
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit launch: %s", hipGetErrorString(e));
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit: %s", hipGetErrorString(e));
-  struct { int32_t status, pad; double cond; } info;
-  const size_t info_off = mpmi::fit_info_offset();
-  e = hipMemcpy(&info, (char*)ctx->fit_work + info_off, sizeof info, hipMemcpyDeviceToHost);
+  mpmi::FitInfo info;
+  e = hipMemcpy(&info, (char*)ctx->fit_work + mpmi::fit_info_offset(), sizeof info, hipMemcpyDeviceToHost);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit readback: %s", hipGetErrorString(e));
-  if (cond_out) *cond_out = info.cond;
+  if (cond_out) *cond_out = condition(info);
   if (info.status != MPMI_OK)
     return fail(ctx, MPMI_ESINGULAR, "scaled Gram matrix is not numerically positive definite");
   return ok(ctx);
@@ -350,10 +357,10 @@ mpmi_status koopman_fit_lifted(mpmi_ctx ctx, const mpmi_system* sys, const doubl
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit_lifted launch: %s", hipGetErrorString(e));
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit_lifted: %s", hipGetErrorString(e));
-  struct { int32_t status, pad; double cond; } info;
+  mpmi::FitInfo info;
   e = hipMemcpy(&info, (char*)ctx->fit_work + mpmi::fit_info_offset(), sizeof info, hipMemcpyDeviceToHost);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit_lifted readback: %s", hipGetErrorString(e));
-  if (cond_out) *cond_out = info.cond;
+  if (cond_out) *cond_out = condition(info);
   if (info.status != MPMI_OK)
     return fail(ctx, MPMI_ESINGULAR, "scaled Gram matrix is not numerically positive definite");
   return ok(ctx);

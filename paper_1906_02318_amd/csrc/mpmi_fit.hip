@@ -2,16 +2,15 @@
 // least squares as in extended DMD).  Three launches:
 //   1. gram:   every workgroup lifts tiles of 64 rows into LDS (psi computed on
 //              the fly, never materialised in HBM) and accumulates its share
-//              of Z^T Z restricted to the first D rows, Z = [Psi | Y], in
-//              4 x 6 register blocks, one wave lifting the next tile while
-//              three accumulate the current one;
+//              of Z^T Z restricted to the first D rows, Z = [Psi | targets], in
+//              16 x 16 blocks on the FP64 matrix cores, one or two waves
+//              lifting the next tile while the others accumulate;
 //   2. reduce: partial sums added in a fixed order (deterministic);
-//   3. solve:  one workgroup: RMS column scaling, ridge, Cholesky of the
-//              scaled Gram matrix in registers, then, one wave per task, the two
-//              triangular solves per right-hand side and unscaling, power
-//              iteration on the Gram matrix and, after all four waves form
-//              its inverse from the factor's inverse, on that, for the
-//              condition number.
+//   3. solve:  RMS column scaling, ridge, blocked Cholesky of the scaled Gram
+//              matrix, the triangular solves of all right-hand sides at once
+//              and unscaling, and the extreme eigenvalues (power iteration
+//              on the Gram matrix and on its inverse) for
+//              the condition number.
 #include <hip/hip_runtime.h>
 
 #include "mpmi_launch.hpp"
@@ -20,15 +19,10 @@ namespace mpmi {
 
 constexpr int kFitRows = 64;       // rows per LDS tile
 constexpr int kFitBlocks = 256;    // maximum partial-sum workgroups
-constexpr int kFitCols = MPMI_MAX_DIM + MPMI_MAX_STATE;  // D + n <= 72
-constexpr int kFitThreads = 256;  // four waves: the solve kernel gives each a task
-static_assert(kFitThreads == 4 * 64, "solve_kernel assigns tasks to exactly four waves");
+constexpr int kFitThreads = 256;  // the solve kernel: four waves share its block products
+static_assert(kFitThreads == 4 * 64 && kFitThreads == 4 * MPMI_MAX_DIM, "solve_kernel's work split");
 
-struct FitInfo {
-  int32_t status;
-  int32_t pad;
-  double cond;
-};
+static_assert(MPMI_MAX_STATE <= 16, "the state's target columns are one 16-column block");
 
 // psi(x, u) of one transition in FP64, the FP32 path's feature order,
 // written to z (an LDS row) from the row's state xr[n] and input ur[m].  The
@@ -44,134 +38,221 @@ __device__ __forceinline__ double custom_atom(const mpmi_system& sys, int q, con
   return 1.0;
 }
 
+// HALF 0 writes the features without a sine or cosine (custom bases: the
+// first half), HALF 1 the others: two waves lift a tile.  The sine and cosine
+// of an angle come from one call.
+template <int HALF>
 __device__ __forceinline__ void lift_row(const mpmi_system& sys, const double* __restrict__ xr,
                                          const double* __restrict__ ur, double* z) {
   const int basis = sys.basis, n = sys.n_state, m = sys.n_input;
   if (basis == MPMI_BASIS_CUSTOM) {
-    for (int f = 0; f < sys.dim; ++f)
+    const int mid = sys.dim / 2;
+    for (int f = HALF ? mid : 0; f < (HALF ? sys.dim : mid); ++f)
       z[f] = custom_atom(sys, sys.feat_a[f], xr, ur) * custom_atom(sys, sys.feat_b[f], xr, ur);
     return;
   }
   if (basis == MPMI_BASIS_LINEAR) {
-    for (int k = 0; k < n; ++k) z[k] = xr[k];
-    for (int k = 0; k < m; ++k) z[n + k] = ur[k];
+    if constexpr (HALF == 0) {
+      for (int k = 0; k < n; ++k) z[k] = xr[k];
+      for (int k = 0; k < m; ++k) z[n + k] = ur[k];
+    }
     return;
   }
   if (basis == MPMI_BASIS_BALANCE_BOT) {
-    const double w[5] = {xr[0], xr[1], xr[2], xr[3], ur[0]};
+    if constexpr (HALF == 0) {
+      const double w[5] = {xr[0], xr[1], xr[2], xr[3], ur[0]};
+      int f = 0;
+      z[f++] = 1.0;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) z[f++] = w[k];
+#pragma unroll
+      for (int k = 0; k < 5; ++k)
+#pragma unroll
+        for (int l = k; l < 5; ++l) z[f++] = w[k] * w[l];
+    }
+    return;
+  }
+  if constexpr (HALF == 0) {
+    const double w[8] = {xr[0], xr[1], xr[2], xr[3], xr[4], xr[5], ur[0], ur[1]};
     int f = 0;
     z[f++] = 1.0;
 #pragma unroll
-    for (int k = 0; k < 5; ++k) z[f++] = w[k];
+    for (int k = 0; k < 8; ++k) z[f++] = w[k];
 #pragma unroll
-    for (int k = 0; k < 5; ++k)
+    for (int k = 0; k < 8; ++k)
 #pragma unroll
-      for (int l = k; l < 5; ++l) z[f++] = w[k] * w[l];
-    return;
+      for (int l = k; l < 8; ++l) z[f++] = w[k] * w[l];
+  } else {
+    int f = 45;
+    double sp, cp, sd, cd;
+    sincos(xr[2], &sp, &cp);
+    sincos(ur[0], &sd, &cd);
+    const double vx = xr[3], vy = xr[4], r = xr[5], a = ur[1];
+    z[f++] = sp; z[f++] = cp; z[f++] = sd; z[f++] = cd;
+    z[f++] = sp * vx; z[f++] = sp * vy; z[f++] = sp * r; z[f++] = sp * a;
+    z[f++] = cp * vx; z[f++] = cp * vy; z[f++] = cp * r; z[f++] = cp * a;
+    z[f++] = sd * vx; z[f++] = sd * vy; z[f++] = sd * r;
+    z[f++] = cd * vx; z[f++] = cd * vy; z[f++] = cd * r;
+    z[f++] = a * sd;
   }
-  const double w[8] = {xr[0], xr[1], xr[2], xr[3], xr[4], xr[5], ur[0], ur[1]};
-  int f = 0;
-  z[f++] = 1.0;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) z[f++] = w[k];
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-#pragma unroll
-    for (int l = k; l < 8; ++l) z[f++] = w[k] * w[l];
-  const double sp = sin(w[2]), cp = cos(w[2]), sd = sin(w[6]), cd = cos(w[6]);
-  const double vx = w[3], vy = w[4], r = w[5], a = w[7];
-  z[f++] = sp; z[f++] = cp; z[f++] = sd; z[f++] = cd;
-  z[f++] = sp * vx; z[f++] = sp * vy; z[f++] = sp * r; z[f++] = sp * a;
-  z[f++] = cp * vx; z[f++] = cp * vy; z[f++] = cp * r; z[f++] = cp * a;
-  z[f++] = sd * vx; z[f++] = sd * vy; z[f++] = sd * r;
-  z[f++] = cd * vx; z[f++] = cd * vy; z[f++] = cd * r;
-  z[f++] = a * sd;
 }
 
-// Register blocks of the accumulation: thread t of waves 1..3 owns rows
-// a0 .. a0 + 3 by columns b0 .. b0 + 5 of Z^T Z, so a tile row costs it 10
-// LDS reads for 24 FMAs; the 16 x 12 blocks fill those three waves exactly.
-// Wave 0 lifts the next tile into the other LDS buffer meanwhile, so a tile
-// costs the longer of the lift and the accumulation, not their sum.  Each
-// entry still sums the rows in their order.
-constexpr int kGa = 4, kGb = 6;
-constexpr int kGaBlocks = MPMI_MAX_DIM / kGa;            // 16
-constexpr int kGbBlocks = (kFitCols + kGb - 1) / kGb;    // 12
-constexpr int kZCols = kGbBlocks * kGb;                  // 72: every block's columns lie in the row
-constexpr int kZStride = kZCols + 2;                     // 16-byte aligned rows
-static_assert(kGaBlocks * kGbBlocks == kFitThreads - 64, "one register block per thread of waves 1..3");
-static_assert(MPMI_MAX_DIM % kGa == 0, "feature blocks");
-static_assert(kFitRows == 64, "wave 0 lifts one row per lane");
+// Accumulation on v_mfma_f64_16x16x4f64.  A tile of 64 rows of Z = [Psi | RHS]
+// sits in LDS as 16-column blocks (Psi padded with zero columns to four
+// blocks, the right-hand sides to RB); an MFMA k-step takes four rows, and its
+// A and B operands are the same read of a column block (lane l: row l / 16,
+// column l % 16).  On gfx950 the instruction is a chain of four FMAs in k order
+// (measured: 51,200 results of operands of mixed magnitude, none different),
+// so every entry sums the rows in their order, one rounding each, exactly as a
+// scalar FMA loop does.  Only the blocks on and above the diagonal of
+// Psi' Psi are formed (a product commutes, so the mirrored entry has the same
+// bits).  MFMA and vector FP64 run at the same rate here; what the MFMA saves
+// is LDS reads: at most two 8-byte reads per 16 FMAs of a lane against 10 per
+// 24 for a 4 x 6 register block, which bound the kernel before.  MW waves share
+// the blocks and LW waves lift the next tile meanwhile (waves 0 and 1: Psi;
+// waves 2 and 3 of the lifted operator: its right-hand sides); the row stride
+// is odd, so a wave's writes of one feature use every bank.  The times
+// stand at fit_columns.
+constexpr int kPsiBlocks = MPMI_MAX_DIM / 16;  // 4
+static_assert(MPMI_MAX_DIM == 64, "four 16-column blocks of features");
+static_assert(kFitRows == 64, "a lifting wave takes one row per lane");
 
-// Right-hand sides: ny columns, either Y itself (yc0 < 0; ny = n) or, for the
-// lifted operator, features yc0 .. yc0 + ny - 1 of psi(Y_t, U_t) (the input
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+// Lane l's element of column block cb of the four rows of k-step ks: both the
+// A operand (row = feature) and the B operand (column) of the Gram products.
+template <int STRIDE>
+__device__ __forceinline__ double gram_frag(const double (*Z)[STRIDE], int ks, int cb, int lane) {
+  return Z[4 * ks + (lane >> 4)][16 * cb + (lane & 15)];
+}
+
+// Right-hand sides: ny columns, either Y itself (LIFTED false; ny = n <= 8)
+// or, for the lifted operator, the ny = D features psi(Y_t, U_t) (the input
 // held over the step), lifted on the fly like the rows of Psi.
-__global__ void __launch_bounds__(kFitThreads)
-gram_kernel(mpmi_system sys, int D, int ny, int yc0, const double* __restrict__ X, const double* __restrict__ U,
+template <bool LIFTED>
+struct GramShape {
+  static constexpr int RB = LIFTED ? 4 : 1;               // right-hand-side blocks
+  static constexpr int MW = LIFTED ? 8 : 4;               // waves on the products
+  static constexpr int LW = LIFTED ? 4 : 2;               // waves lifting
+  static constexpr int kTiles = 10 + kPsiBlocks * RB;     // 10 on and above the diagonal
+  static constexpr int kPerWave = (kTiles + MW - 1) / MW;
+  static constexpr int kStride = 16 * (kPsiBlocks + RB) + 1;
+  static constexpr int kThreads = 64 * (MW + LW);
+};
+
+template <bool LIFTED>
+__global__ void __launch_bounds__(GramShape<LIFTED>::kThreads)
+gram_kernel(mpmi_system sys, int D, int ny, const double* __restrict__ X, const double* __restrict__ U,
             const double* __restrict__ Y, long long T, double* __restrict__ part) {
-  __shared__ __attribute__((aligned(16))) double Z[2][kFitRows][kZStride];
+  using GS = GramShape<LIFTED>;
+  __shared__ __attribute__((aligned(16))) double Z[2][kFitRows][GS::kStride];
   const int n = sys.n_state, m = sys.n_input;
   const int C = D + ny;
   const int E = D * C;
-  const bool lifter = threadIdx.x < 64;
-  const int blk = (int)threadIdx.x - 64;
-  const int ab = blk / kGbBlocks, bb = blk % kGbBlocks;
-  const int a0 = ab * kGa, b0 = bb * kGb;
-  const bool active = !lifter && a0 < D && b0 < C;
-  double acc[kGa][kGb];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool lifter = wave < GS::LW;
+  const int mw = wave - GS::LW;
+  // This wave's blocks: number q is (I, J), J < 4 a feature block (I <= J, in
+  // column order), J >= 4 right-hand-side block J - 4.
+  f64x4_t acc[GS::kPerWave];
+  int bi[GS::kPerWave], bj[GS::kPerWave];
+  bool on[GS::kPerWave];
 #pragma unroll
-  for (int i = 0; i < kGa; ++i)
-#pragma unroll
-    for (int j = 0; j < kGb; ++j) acc[i][j] = 0.0;
+  for (int k = 0; k < GS::kPerWave; ++k) {
+    // A wave with fewer blocks repeats block 0 and drops it: no branch stands
+    // between the products and their LDS reads.
+    const int q0 = mw + GS::MW * k, q = q0 < 0 || q0 >= GS::kTiles ? 0 : q0;
+    int i, j;
+    if (q < 10) {
+      j = q < 1 ? 0 : (q < 3 ? 1 : (q < 6 ? 2 : 3));
+      i = q - j * (j + 1) / 2;
+    } else {
+      i = (q - 10) & 3;
+      j = 4 + ((q - 10) >> 2);
+    }
+    bi[k] = i;
+    bj[k] = j;
+    on[k] = !lifter && q == q0;
+    acc[k] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  }
   const long long ntiles = (T + kFitRows - 1) / kFitRows;
   // This workgroup's tiles: blockIdx.x + k * gridDim.x, k = 0 .. count - 1.
   const long long count = blockIdx.x < ntiles ? (ntiles - 1 - blockIdx.x) / gridDim.x + 1 : 0;
   auto lift_tile = [&](long long k, int buf) {
-    const long long r = (blockIdx.x + k * gridDim.x) * kFitRows + threadIdx.x;
-    double* z = Z[buf][threadIdx.x];
-    if (r < T) {
-      if (yc0 >= 0) {
-        // psi(Y_t, U_t) into the row first, its chunk moved past the D features
-        lift_row(sys, Y + r * n, U + r * m, z);
-        for (int q = 0; q < ny; ++q) z[D + q] = z[yc0 + q];
-      } else {
-        for (int q = 0; q < ny; ++q) z[D + q] = Y[r * n + q];
-      }
-      lift_row(sys, X + r * n, U + r * m, z);
-    } else {
-      for (int q = 0; q < C; ++q) z[q] = 0.0;
+    const long long r = (blockIdx.x + k * gridDim.x) * kFitRows + lane;
+    double* z = Z[buf][lane];
+    double* y = z + 16 * kPsiBlocks;
+    if (r >= T) {
+      for (int q = wave; q < GS::kStride - 1; q += GS::LW) z[q] = 0.0;
+      return;
     }
-    for (int q = C; q < kZCols; ++q) z[q] = 0.0;
+    if (wave == 0) {
+      lift_row<0>(sys, X + r * n, U + r * m, z);
+      for (int q = D; q < 16 * kPsiBlocks; ++q) z[q] = 0.0;
+      if constexpr (!LIFTED) {
+        for (int q = 0; q < ny; ++q) y[q] = Y[r * n + q];
+        for (int q = ny; q < 16 * GS::RB; ++q) y[q] = 0.0;
+      }
+    } else if (wave == 1) {
+      lift_row<1>(sys, X + r * n, U + r * m, z);
+    } else if (wave == 2) {
+      lift_row<0>(sys, Y + r * n, U + r * m, y);
+      for (int q = D; q < 16 * GS::RB; ++q) y[q] = 0.0;
+    } else {
+      lift_row<1>(sys, Y + r * n, U + r * m, y);
+    }
   };
   if (lifter && count > 0) lift_tile(0, 0);
   __syncthreads();
   for (long long k = 0; k < count; ++k) {
     if (lifter) {
       if (k + 1 < count) lift_tile(k + 1, (int)((k + 1) & 1));
-    } else if (active) {
-      const int buf = (int)(k & 1);
-#pragma unroll 4
-      for (int rr = 0; rr < kFitRows; ++rr) {
-        double av[kGa], bv[kGb];
+    } else {
+      const double(*z)[GS::kStride] = Z[(int)(k & 1)];
+      // The next k-step's operands are read before this one's products; the
+      // scheduling barrier keeps the reads there (left to itself the compiler
+      // reads each pair just before its product and waits for it).
+      double fa[2][GS::kPerWave], fb[2][GS::kPerWave];
 #pragma unroll
-        for (int i = 0; i < kGa; ++i) av[i] = Z[buf][rr][a0 + i];
+      for (int q = 0; q < GS::kPerWave; ++q) {
+        fa[0][q] = gram_frag<GS::kStride>(z, 0, bi[q], lane);
+        fb[0][q] = gram_frag<GS::kStride>(z, 0, bj[q], lane);
+      }
 #pragma unroll
-        for (int j = 0; j < kGb; ++j) bv[j] = Z[buf][rr][b0 + j];
+      for (int ks = 0; ks < kFitRows / 4; ++ks) {
+        const int cur = ks & 1;
+        if (ks + 1 < kFitRows / 4)
 #pragma unroll
-        for (int i = 0; i < kGa; ++i)
+          for (int q = 0; q < GS::kPerWave; ++q) {
+            fa[cur ^ 1][q] = gram_frag<GS::kStride>(z, ks + 1, bi[q], lane);
+            fb[cur ^ 1][q] = gram_frag<GS::kStride>(z, ks + 1, bj[q], lane);
+          }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int j = 0; j < kGb; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
+        for (int q = 0; q < GS::kPerWave; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[cur][q], fb[cur][q], acc[q], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     __syncthreads();
   }
-  if (!active) return;
+  if (lifter) return;
+  // Result layout: lane l holds column l % 16 of rows 4 r + l / 16.
   double* out = part + (size_t)blockIdx.x * E;
 #pragma unroll
-  for (int i = 0; i < kGa; ++i)
+  for (int q = 0; q < GS::kPerWave; ++q) {
+    if (!on[q]) continue;
+    const int col = 16 * (bj[q] & 3) + (lane & 15);
+    const bool rhs = bj[q] >= 4;
+    if (col >= (rhs ? ny : D)) continue;
 #pragma unroll
-    for (int j = 0; j < kGb; ++j)
-      if (a0 + i < D && b0 + j < C) out[(a0 + i) * C + b0 + j] = acc[i][j];
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * bi[q] + 4 * r + (lane >> 4);
+      if (row >= D) continue;
+      out[row * C + (rhs ? D + col : col)] = acc[q][r];
+      if (!rhs && bi[q] != bj[q]) out[col * C + row] = acc[q][r];
+    }
+  }
 }
 
 // tot[e] = sum over the parts of part[p][e], in a fixed order: the
@@ -209,355 +290,386 @@ __device__ __forceinline__ double lane_bcast(double x, int k) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// One step of a DPP sum: x plus the value CTRL selects (0 where the source
-// is outside the row or the row and bank masks).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add(double x) {
+// ---------------------------------------------------------------------------
+// The solve: 64 x 64 matrices in LDS as 16-wide panels.  Inside a panel the
+// 16 steps run in one wave's registers; everything a panel does to the rest of
+// a matrix is a product of 16-wide blocks on v_mfma_f64_16x16x4f64.  That
+// instruction adds its four products in k order with one rounding each (see
+// the Gram kernel), so a blocked factorisation or substitution gives every
+// entry the same FMAs in the same order as the step-by-step loop.
+//
+// Two workgroups run side by side: workgroup 0 factors, solves and estimates
+// the least eigenvalue, workgroup 1 the largest.  One workgroup took 92 us
+// (race car, D = 64): the factorisation 27 (a barrier per two columns), the
+// inverse of the factor 22, its product 6, and twice 60 serial steps of power
+// iteration, 28 and 24.  Its bound is the serial chain of 64 pivots, not
+// arithmetic: all of its products are ~2 MFLOP.
+// ---------------------------------------------------------------------------
+constexpr int kMs = MPMI_MAX_DIM + 2;  // LDS row stride of a 64 x 64 matrix
+typedef double MatRow[kMs];
+
+// One 16 x 16 block acc += A B over 4 NS k-steps of four: a(i, k) the value of
+// lane (row i, k), b(k, j) that of lane (k, column j).  The operands of four
+// k-steps are read before their products, the next four meanwhile.
+template <int NS, class FA, class FB>
+__device__ __forceinline__ f64x4_t block_fma(f64x4_t acc, FA a, FB b) {
+  const int lane = threadIdx.x & 63, k0 = lane >> 4, ij = lane & 15;
+  double fa[2][4], fb[2][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    fa[0][q] = a(ij, 4 * q + k0);
+    fb[0][q] = b(4 * q + k0, ij);
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    if (s + 1 < NS)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        fa[(s + 1) & 1][q] = a(ij, 16 * (s + 1) + 4 * q + k0);
+        fb[(s + 1) & 1][q] = b(16 * (s + 1) + 4 * q + k0, ij);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[s & 1][q], fb[s & 1][q], acc, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return acc;
+}
+
+// Cholesky of the D x D matrix in A (lower triangle), right-looking in panels
+// of 16 columns.  With c_k column k before its own step and d_k its pivot,
+// step k subtracts c_ik (c_jk / d_k) from every entry (i, j) with i >= j > k;
+// the columns stay unscaled (c_k below the diagonal, pivots in piv[]).  Wave
+// 0 holds a panel as one row per lane; step k's multipliers reach the panel's
+// other columns by lane broadcast, and Tp[j][k] keeps them for the block
+// products.  Called by the whole workgroup (four waves).
+__device__ __forceinline__ void factor(MatRow* A, double (*Tp)[18], double* piv, int D, double pivot_floor, int* bad) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int p = 0; 16 * p < D; ++p) {
+    const int c0 = 16 * p;
+    if (wave == 0) {
+      double a[16], pv = 1.0;
+      bool low = false;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) a[k] = A[lane][c0 + k];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        // A pivot below the floor marks the fit singular and is replaced by 1
+        // (so is a column past D: all zero, its multipliers stay zero).
+        double d = lane_bcast(a[k], c0 + k);
+        const bool ok = d > pivot_floor;
+        low |= !ok & (c0 + k < D);
+        d = ok ? d : 1.0;
+        pv = lane == c0 + k ? d : pv;
+        // 1 / d: the hardware estimate and two Newton steps (d > 0, normal).
+        double rd = __builtin_amdgcn_rcp(d);
+        rd = fma(rd, fma(-d, rd, 1.0), rd);
+        rd = fma(rd, fma(-d, rd, 1.0), rd);
+        const double t = a[k] * rd;
+#pragma unroll
+        for (int j = k + 1; j < 16; ++j) a[j] = fma(-a[k], lane_bcast(t, c0 + j), a[j]);
+        Tp[lane][k] = t;
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) A[lane][c0 + k] = a[k];
+      if (lane >= c0 && lane < c0 + 16) piv[lane] = pv;
+      if (low && lane == 0) *bad = 1;
+    }
+    __syncthreads();
+    // Blocks (I, J), I >= J > p, spread over the waves.
+    int q = 0;
+    for (int J = p + 1; J < 4; ++J)
+      for (int I = J; I < 4; ++I, ++q) {
+        if ((q & 3) != wave || 16 * I >= D) continue;
+        f64x4_t acc;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = A[16 * I + 4 * r + (lane >> 4)][16 * J + (lane & 15)];
+        acc = block_fma<1>(acc, [&](int i, int k) { return -A[16 * I + i][c0 + k]; },
+                        [&](int k, int j) { return Tp[16 * J + j][k]; });
+#pragma unroll
+        for (int r = 0; r < 4; ++r) A[16 * I + 4 * r + (lane >> 4)][16 * J + (lane & 15)] = acc[r];
+      }
+    __syncthreads();
+  }
+}
+
+// One step of a DPP sum over a quad: x plus the lane CTRL selects.
+template <int CTRL>
+__device__ __forceinline__ double quad_add(double x) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROW_MASK, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROW_MASK, 0xF, false);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, true);
   return x + __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// Sum over the 64 lanes (every lane active), the same value in every lane:
-// shifts by 1, 2, 4, 8 within each row of 16, the row broadcasts of lanes 15
-// and 31, then lane 63's total read back.  A fixed order; no LDS round trip.
-__device__ __forceinline__ double wave_sum(double x) {
-  x = dpp_add<0x111, 0xF>(x);  // row_shr:1
-  x = dpp_add<0x112, 0xF>(x);  // row_shr:2
-  x = dpp_add<0x114, 0xF>(x);  // row_shr:4
-  x = dpp_add<0x118, 0xF>(x);  // row_shr:8
-  x = dpp_add<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
-  x = dpp_add<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
-  return lane_bcast(x, 63);
-}
-
-// The factor as lane i keeps it in registers: m[k] = L_ik for k < i (its
-// row) and L_ki for k > i (its column), zero past D.  The forward solve uses
-// lane i's residual only up to step i and the backward solve only down to
-// step i, so each may subtract the other half's entries after that point; a
-// solve step is then a multiply, a broadcast and an FMA, with no memory
-// access in the serial chain.
-__device__ __forceinline__ void load_packed_factor(const double (&L)[MPMI_MAX_DIM][MPMI_MAX_DIM + 1], int D, int lane,
-                                                   double (&m)[MPMI_MAX_DIM]) {
-  const bool own = lane < D;
+// The Rayleigh quotient (w . v) / (v . v), w = A v, of the last of 60 steps of
+// power iteration from v0 on the symmetric matrix in M (zero past D).  Four
+// lanes hold a row, 16 columns each in registers; the iterate goes from one
+// LDS buffer to the other, so a step is eight broadcast reads, 16 FMAs, a quad
+// sum and one barrier.  M is taken times the power of two that brings its
+// trace, which bounds its eigenvalues, into [1, 2) (exact; the quotient scales
+// with it): the iterate shrinks by at most 2^-6 a step along the leading
+// eigenvector and needs no normalisation.  Called by the whole workgroup; the
+// same value in every thread.
+__device__ __forceinline__ double power_rayleigh(const MatRow* M, double v0, double (*v)[MPMI_MAX_DIM]) {
+  const int t = threadIdx.x, lane = t & 63, row = t >> 2, c = 16 * (t & 3);
+  double tr = M[lane][lane];
 #pragma unroll
-  for (int k = 0; k < MPMI_MAX_DIM; ++k)
-    m[k] = (own && k < D && k != lane) ? (k < lane ? L[lane][k] : L[k][lane]) : 0.0;
-}
-
-// L L^T y = b: lane i holds b_i and rinv = 1 / L_ii (0 past D) and returns
-// y_i.  Step k of the forward solve fixes z_k = r_k / L_kk once lane k's
-// residual is complete; the backward solve runs from the last row up.
-__device__ __forceinline__ double packed_cholesky_solve(const double (&m)[MPMI_MAX_DIM], int lane, double rinv,
-                                                        double b) {
-  double r = b, z = 0.0;
+  for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o, 64);
+  const int e = tr > 0.0 && tr < 1e300 ? ilogb(tr) : 0;
+  const double sc = ldexp(1.0, -e);
+  double m[16];
 #pragma unroll
-  for (int k = 0; k < MPMI_MAX_DIM; ++k) {  // L z = b
-    const double zk = lane_bcast(r * rinv, k);
-    z = lane == k ? zk : z;
-    r = fma(-m[k], zk, r);
-  }
-  double y = 0.0;
-  r = z;
-#pragma unroll
-  for (int k = MPMI_MAX_DIM - 1; k >= 0; --k) {  // L^T y = z
-    const double yk = lane_bcast(r * rinv, k);
-    y = lane == k ? yk : y;
-    r = fma(-m[k], yk, r);
-  }
-  return y;
-}
-
-// Orders this wave's LDS accesses before and after it (the lanes of a wave
-// exchange values through LDS with no workgroup barrier).
-__device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-// Largest eigenvalue of the symmetric matrix whose row `lane` the lane holds
-// in a[] (rows and columns past D zero) by 60 steps of power iteration from
-// v0: the Rayleigh quotient (w . v) / (v . v), w = A v, of the last step.
-// The iterate reaches every lane through vb (this wave's 64 doubles of LDS)
-// as broadcast reads.  Between steps it is rescaled by the hardware's
-// reciprocal square root of w . w: the quotient does not depend on the
-// scale, so no exact square root or division sits in the steps' chain.
-__device__ __forceinline__ double power_rayleigh(const double (&a)[MPMI_MAX_DIM], bool own, int lane, double v0,
-                                                 double* vb) {
-  double v = own ? v0 : 0.0, w = 0.0;
+  for (int k = 0; k < 16; ++k) m[k] = M[row][c + k] * sc;
+  if (t < MPMI_MAX_DIM) v[0][t] = v0;
+  __syncthreads();
   for (int it = 0; it < 60; ++it) {
-    vb[lane] = v;
-    wave_lds_sync();
-    double w0 = 0.0, w1 = 0.0, w2 = 0.0, w3 = 0.0;
+    const double* x = v[it & 1] + c;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
 #pragma unroll
-    for (int j = 0; j < MPMI_MAX_DIM; j += 4) {
-      w0 = fma(a[j], vb[j], w0);
-      w1 = fma(a[j + 1], vb[j + 1], w1);
-      w2 = fma(a[j + 2], vb[j + 2], w2);
-      w3 = fma(a[j + 3], vb[j + 3], w3);
+    for (int k = 0; k < 16; k += 4) {
+      s0 = fma(m[k], x[k], s0);
+      s1 = fma(m[k + 1], x[k + 1], s1);
+      s2 = fma(m[k + 2], x[k + 2], s2);
+      s3 = fma(m[k + 3], x[k + 3], s3);
     }
-    w = (w0 + w1) + (w2 + w3);
-    if (it + 1 < 60) v = w * __builtin_amdgcn_rsq(wave_sum(w * w));
+    const double s = quad_add<0x4E>(quad_add<0xB1>((s0 + s1) + (s2 + s3)));  // lanes xor 1, then xor 2
+    if ((t & 3) == 0) v[(it + 1) & 1][row] = s;
+    __syncthreads();
   }
-  return wave_sum(w * v) / wave_sum(v * v);
+  // v[1] holds the iterate before the last step, v[0] the last product.
+  double a = v[1][lane] * v[0][lane], b = v[1][lane] * v[1][lane];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, 64);
+    b += __shfl_xor(b, o, 64);
+  }
+  return ldexp(a / b, e);
 }
 
-// One workgroup.  tot holds [D][C]: G = columns 0..D-1, A = columns D..D+n-1.
+// tot holds [D][C]: G = columns 0..D-1, A = columns D..D+ny-1.  RB: 16-column
+// blocks of right-hand sides (ny <= 16 RB).  K [D][ny].
+template <int RB>
 __global__ void __launch_bounds__(kFitThreads)
-solve_kernel(int n, int D, long long T, double ridge, const double* __restrict__ tot, double* __restrict__ K,
+solve_kernel(int ny, int D, long long T, double ridge, const double* __restrict__ tot, double* __restrict__ K,
              FitInfo* __restrict__ info) {
-  __shared__ double L[MPMI_MAX_DIM][MPMI_MAX_DIM + 1];
-  __shared__ __attribute__((aligned(16))) double Lt[MPMI_MAX_DIM][MPMI_MAX_DIM + 2];  // (L^-1)^T (wave 0)
-  __shared__ __attribute__((aligned(16))) double Lz[MPMI_MAX_DIM][MPMI_MAX_DIM + 2];  // strictly lower L, then G_s^-1
-  __shared__ double B[MPMI_MAX_DIM][MPMI_MAX_STATE];
-  __shared__ double sc[MPMI_MAX_DIM], srinv[MPMI_MAX_DIM], piv[MPMI_MAX_DIM];
-  __shared__ __attribute__((aligned(16))) double vbuf[2][MPMI_MAX_DIM];
+  constexpr int kXs = 16 * RB + MPMI_MAX_DIM + 2;  // right-hand sides, then the identity
+  __shared__ __attribute__((aligned(16))) double A[MPMI_MAX_DIM][kMs];   // G_s, then the factor
+  __shared__ __attribute__((aligned(16))) double X[MPMI_MAX_DIM][kXs];
+  __shared__ __attribute__((aligned(16))) double M[MPMI_MAX_DIM][kMs];   // G_s^-1 (workgroup 1: G_s)
+  __shared__ double Tp[MPMI_MAX_DIM][18];
+  __shared__ double sc[MPMI_MAX_DIM], rinv[MPMI_MAX_DIM], piv[MPMI_MAX_DIM];
+  __shared__ __attribute__((aligned(16))) double vv[2][MPMI_MAX_DIM];
   __shared__ int bad;
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
-  const int C = D + n;
-  if (t == 0) bad = 0;
-  for (int f = t; f < D; f += blockDim.x) {
-    const double g = tot[(size_t)f * C + f];
-    const double s = sqrt(g / (double)T);
-    sc[f] = s > 0.0 ? s : 1.0;
-  }
-  __syncthreads();
-  // Thread (wave w, lane j) holds entries (w + 4r, j), r = 0..15, of G_s in
-  // registers through the factorisation; G_s itself also goes to L, whose
-  // upper triangle the condition estimate reads.  Loads use clamped (valid)
-  // indices so that none waits behind a branch.
+  const int C = D + ny;
+  // Loads use clamped (valid) indices so that none waits behind a branch, and
+  // all are issued before the scale factors are formed.
   constexpr int kRowsPerWave = MPMI_MAX_DIM / 4;
   double a[kRowsPerWave];
-  {
-    const int jc = min(lane, D - 1);
+  const int jc = min(lane, D - 1);
 #pragma unroll
-    for (int r = 0; r < kRowsPerWave; ++r) a[r] = tot[(size_t)min(wave + 4 * r, D - 1) * C + jc];
+  for (int r = 0; r < kRowsPerWave; ++r) a[r] = tot[(size_t)min(wave + 4 * r, D - 1) * C + jc];
+  constexpr int kRhs = 4 * RB;  // right-hand-side entries per thread
+  double b[kRhs];
 #pragma unroll
-    for (int r = 0; r < kRowsPerWave; ++r) {
-      const int i = wave + 4 * r;
-      a[r] = (i < D && lane < D) ? a[r] / (sc[i] * sc[lane]) + (i == lane ? ridge : 0.0) : 0.0;
-      if (i < D && lane < D) L[i][lane] = a[r];
-    }
+  for (int r = 0; r < kRhs; ++r) {
+    const int i = (t + kFitThreads * r) / (16 * RB), j = (t + kFitThreads * r) % (16 * RB);
+    b[r] = tot[(size_t)min(i, D - 1) * C + D + min(j, ny - 1)];
   }
-  for (int e = t; e < D * n; e += blockDim.x) {
-    const int i = e / n, j = e % n;
-    B[i][j] = tot[(size_t)i * C + D + j] / sc[i];
+  if (t == 0) bad = 0;
+  if (t < MPMI_MAX_DIM) {
+    const double g = tot[(size_t)jc * C + jc];
+    const double s = sqrt(g / (double)T);
+    sc[t] = s > 0.0 ? s : 1.0;
+    piv[t] = 1.0;
   }
-  // Cholesky, right-looking, on the register copy; one barrier per two
-  // columns.  With c_k column k before its own step (entries not yet
-  // scaled) and d_k its pivot, step k subtracts c_ik c_jk / d_k from every
-  // entry (i, j) with j > k (entries above the diagonal become garbage and
-  // are never read).  Columns k and k + 1 as they stand before step k are
-  // published in LDS by their owners, the threads of lanes k and k + 1, as
-  // col[.][0 or 1][w][r] = entry (w + 4r, column).  Each thread then applies
-  // steps k and k + 1 itself, forming the step-k update of column k + 1 that
-  // it needs exactly as lane k + 1 forms it (so the factor is the
-  // one-column-per-step factor, bit for bit); the threads of lanes k + 2 and
-  // k + 3 publish the next pair.  The pair buffers alternate.  The pivots
-  // are kept, and each column is scaled into the factor (L_ik = c_i /
-  // sqrt(d_k), L_kk = sqrt(d_k)) after the loop, off the steps' chain.
-  __shared__ __attribute__((aligned(16))) double col[2][2][4][kRowsPerWave];
-  if (lane < 2)
-#pragma unroll
-    for (int r = 0; r < kRowsPerWave; ++r) col[0][lane][wave][r] = a[r];
   __syncthreads();
-  const double pivot_floor = 1e-14 * (double)T;
-  // A pivot below the floor marks the fit singular and is replaced by 1.
-  auto pivot = [&](double d) {
-    if (!(d > pivot_floor)) {
-      if (t == 0) bad = 1;
-      d = 1.0;
-    }
-    return d;
-  };
-  // 1 / d: the hardware estimate and two Newton steps (d > 0, normal).
-  auto recip = [](double d) {
-    double rd = __builtin_amdgcn_rcp(d);
-    rd = fma(rd, fma(-d, rd, 1.0), rd);
-    return fma(rd, fma(-d, rd, 1.0), rd);
-  };
-  int k = 0;
-  for (; k + 1 < D; k += 2) {
-    const double(*c0)[kRowsPerWave] = col[(k >> 1) & 1][0];
-    const double(*c1)[kRowsPerWave] = col[(k >> 1) & 1][1];
-    const int k1 = k + 1;
-    const double d0 = pivot(c0[k & 3][k >> 2]);
-    const double r0 = recip(d0);
-    const double t01 = c0[k1 & 3][k1 >> 2] * r0;  // step k's multiplier of column k + 1
-    const double d1 = pivot(fma(-c0[k1 & 3][k1 >> 2], t01, c1[k1 & 3][k1 >> 2]));
-    if (t == 0) {
-      piv[k] = d0;
-      piv[k1] = d1;
-    }
-    if (lane > k) {
-      const double tj0 = c0[lane & 3][lane >> 2] * r0;
+  MatRow* const Gs = blockIdx.x == 0 ? A : M;
 #pragma unroll
-      for (int r = 0; r < kRowsPerWave; ++r) a[r] = fma(-c0[wave][r], tj0, a[r]);
-    }
-    if (lane > k1) {
-      const double r1 = recip(d1);
-      const double tj1 = fma(-c0[lane & 3][lane >> 2], t01, c1[lane & 3][lane >> 2]) * r1;
-#pragma unroll
-      for (int r = 0; r < kRowsPerWave; ++r) a[r] = fma(-fma(-c0[wave][r], t01, c1[wave][r]), tj1, a[r]);
-    }
-    if (lane == k + 2 || lane == k + 3)
-#pragma unroll
-      for (int r = 0; r < kRowsPerWave; ++r) col[((k >> 1) + 1) & 1][lane - k - 2][wave][r] = a[r];
+  for (int r = 0; r < kRowsPerWave; ++r) {
+    const int i = wave + 4 * r;
+    Gs[i][lane] = (i < D && lane < D) ? a[r] / (sc[i] * sc[lane]) + (i == lane ? ridge : 0.0) : 0.0;
+  }
+  if (blockIdx.x != 0) {
     __syncthreads();
+    const double lmax = power_rayleigh(M, t < D ? 1.0 + 0.01 * t : 0.0, vv);
+    if (t == 0) info->lmax = lmax;
+    return;
   }
-  if (k < D && t == 0) piv[k] = pivot(col[(k >> 1) & 1][0][k & 3][k >> 2]);  // odd D: the last column
+#pragma unroll
+  for (int r = 0; r < kRhs; ++r) {
+    const int i = (t + kFitThreads * r) / (16 * RB), j = (t + kFitThreads * r) % (16 * RB);
+    X[i][j] = (i < D && j < ny) ? b[r] / sc[i] : 0.0;
+  }
+#pragma unroll
+  for (int r = 0; r < kRowsPerWave; ++r) X[wave + 4 * r][16 * RB + lane] = wave + 4 * r == lane ? 1.0 : 0.0;
   __syncthreads();
-  if (lane < D) {
+  factor(A, Tp, piv, D, 1e-14 * (double)T, &bad);
+  // The columns scaled into the factor: L_ik = c_i / sqrt(d_k), L_kk = sqrt(d_k).
+  {
     const double lkk = sqrt(piv[lane]), rs = 1.0 / lkk;
 #pragma unroll
     for (int r = 0; r < kRowsPerWave; ++r) {
       const int i = wave + 4 * r;
-      a[r] = i == lane ? lkk : a[r] * rs;
+      const double v = A[i][lane];
+      A[i][lane] = (i < D && lane <= i) ? (i == lane ? lkk : v * rs) : 0.0;
     }
-  }
-  // The factor to L (lower triangle and diagonal; G_s stays above), and its
-  // strictly lower part, zero elsewhere, to Lz for the inverse.
-#pragma unroll
-  for (int r = 0; r < kRowsPerWave; ++r) {
-    const int i = wave + 4 * r;
-    if (i < D && lane <= i) L[i][lane] = a[r];
-    Lz[i][lane] = (i < D && lane < i) ? a[r] : 0.0;
+    if (wave == 0) rinv[lane] = lane < D ? rs : 0.0;
   }
   __syncthreads();
-  // Triangular solves and the condition estimate run one wave per task, the
-  // tasks concurrently: lane i owns row i (D <= 64), the wave's lockstep
-  // orders the steps, and the values a step needs from another lane arrive
-  // by lane broadcast or through LDS written by the same wave, so no
-  // workgroup barrier is involved until the inverse is complete.  The factor
-  // is read-only from here on.
-  const bool own = lane < D;
-  const double rinv = own ? 1.0 / L[lane][lane] : 0.0;
-  __shared__ double s_lmax, s_lmin_inv;
-  if (wave >= 2) {
-    // K: waves 2 and 3 solve the right-hand sides c = wave - 2, wave, ...
-    double m[MPMI_MAX_DIM];
-    load_packed_factor(L, D, lane, m);
-    for (int c = wave - 2; c < n; c += 2) {
-      const double k = packed_cholesky_solve(m, lane, rinv, own ? B[lane][c] : 0.0);
-      if (own) K[(size_t)lane * n + c] = k / sc[lane];
+  // Forward substitution L Z = [B | I], in place, a panel of 16 rows at a time:
+  // one column per lane inside the panel (wave w: columns 64 w ..), then
+  // block products for the rows below.
+  constexpr int kCols = 16 * RB + MPMI_MAX_DIM, kColBlocks = kCols / 16;
+  for (int p = 0; p < 4; ++p) {
+    const int c0 = 16 * p;
+    if (t < kCols) {
+      // The panel's diagonal block, a row in each of lanes 0 .. 15, is read
+      // by lane broadcast.
+      double x[16], l[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        x[k] = X[c0 + k][t];
+        l[k] = A[c0 + (lane & 15)][c0 + k];
+      }
+      const double ri = rinv[c0 + (lane & 15)];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        x[k] *= lane_bcast(ri, k);
+#pragma unroll
+        for (int i = k + 1; i < 16; ++i) x[i] = fma(-lane_bcast(l[k], i), x[k], x[i]);
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) X[c0 + k][t] = x[k];
     }
-  } else if (wave == 1) {
-    // Largest eigenvalue of the scaled Gram matrix G_s (from its upper
-    // triangle and the diagonal of L L^T); lane i holds row i.
-    double diag = 0.0;
-    if (own)
-      for (int k = 0; k <= lane; ++k) diag += L[lane][k] * L[lane][k];
-    double grow[MPMI_MAX_DIM];
+    __syncthreads();
+    for (int q = wave; q < (3 - p) * kColBlocks; q += 4) {
+      const int I = p + 1 + q / kColBlocks, J = q % kColBlocks;
+      f64x4_t acc;
 #pragma unroll
-    for (int j = 0; j < MPMI_MAX_DIM; ++j)
-      grow[j] = (own && j < D) ? (lane == j ? diag : (lane < j ? L[lane][j] : L[j][lane])) : 0.0;
-    const double lmax = power_rayleigh(grow, own, lane, 1.0 + 0.01 * lane, vbuf[1]);
-    if (lane == 0) s_lmax = lmax;
-  } else {
-    // Smallest eigenvalue of G_s as 1 / the largest of G_s^-1 = L^-T L^-1
-    // (power iteration on G_s^-1 from the start vector is the inverse
-    // iteration on G_s through the factor).  Here lane c forms column c of
-    // L^-1 by forward substitution into row c of Lt = (L^-1)^T: row k is a
-    // dot product of the strictly lower row k of L with the entries found
-    // so far, over blocks of 16 up to k.  Loops, not unrolled code, so the
-    // task stays in the instruction cache beside the other waves'.
-    srinv[lane] = rinv;
+      for (int r = 0; r < 4; ++r) acc[r] = X[16 * I + 4 * r + (lane >> 4)][16 * J + (lane & 15)];
+      acc = block_fma<1>(acc, [&](int i, int k) { return -A[16 * I + i][c0 + k]; },
+                      [&](int k, int j) { return X[c0 + k][16 * J + j]; });
 #pragma unroll
-    for (int k = 0; k < MPMI_MAX_DIM; ++k) Lt[lane][k] = 0.0;
-    wave_lds_sync();
-    for (int k = 0; k < D; ++k) {
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-      for (int j0 = 0; j0 < k; j0 += 16) {
+      for (int r = 0; r < 4; ++r) X[16 * I + 4 * r + (lane >> 4)][16 * J + (lane & 15)] = acc[r];
+    }
+    __syncthreads();
+  }
+  // G_s^-1 = L^-T L^-1 (the smallest eigenvalue of G_s is 1 / its largest):
+  // block (I, J), I <= J, sums over rows k >= 16 J, L^-1 being zero above its
+  // diagonal.
+  {
+    int q = 0;
+    for (int J = 0; J < 4; ++J)
+      for (int I = 0; I <= J; ++I, ++q) {
+        if ((q & 3) != wave) continue;
+        f64x4_t acc{0.0, 0.0, 0.0, 0.0};
+        for (int k0 = 16 * J; k0 < MPMI_MAX_DIM; k0 += 16)
+          acc = block_fma<1>(acc, [&](int i, int k) { return X[k0 + k][16 * RB + 16 * I + i]; },
+                             [&](int k, int j) { return X[k0 + k][16 * RB + 16 * J + j]; });
 #pragma unroll
-        for (int j = j0; j < j0 + 16; j += 4) {
-          s0 = fma(Lz[k][j], Lt[lane][j], s0);
-          s1 = fma(Lz[k][j + 1], Lt[lane][j + 1], s1);
-          s2 = fma(Lz[k][j + 2], Lt[lane][j + 2], s2);
-          s3 = fma(Lz[k][j + 3], Lt[lane][j + 3], s3);
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * I + 4 * r + (lane >> 4), col = 16 * J + (lane & 15);
+          const bool in = row < D && col < D;
+          M[row][col] = in ? acc[r] : 0.0;
+          M[col][row] = in ? acc[r] : 0.0;
         }
       }
-      Lt[lane][k] = ((k == lane ? 1.0 : 0.0) - ((s0 + s1) + (s2 + s3))) * srinv[k];
-    }
   }
-  __syncthreads();
-  // G_s^-1 into Lz (no longer needed), its rows spread over the four waves:
-  // (G_s^-1)_ji = sum_{k >= j} (L^-1)_ki (L^-1)_kj, lane i of row j, the
-  // entries of L^-1 above the diagonal being zero.
-  for (int j = wave; j < D; j += 4) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    for (int k0 = j & ~15; k0 < MPMI_MAX_DIM; k0 += 16) {
+  // Backward substitution L^T Y = Z on the right-hand sides, rows from the
+  // last up.
+  for (int p = 3; p >= 0; --p) {
+    const int c0 = 16 * p;
+    if (t < 16 * RB) {
+      double x[16], l[16];
 #pragma unroll
-      for (int k = k0; k < k0 + 16; k += 4) {
-        s0 = fma(Lt[lane][k], Lt[j][k], s0);
-        s1 = fma(Lt[lane][k + 1], Lt[j][k + 1], s1);
-        s2 = fma(Lt[lane][k + 2], Lt[j][k + 2], s2);
-        s3 = fma(Lt[lane][k + 3], Lt[j][k + 3], s3);
+      for (int k = 0; k < 16; ++k) {
+        x[k] = X[c0 + k][t];
+        l[k] = A[c0 + (lane & 15)][c0 + k];
       }
-    }
-    Lz[j][lane] = (s0 + s1) + (s2 + s3);
-  }
-  __syncthreads();
-  if (wave == 0) {
-    double gi[MPMI_MAX_DIM];
+      const double ri = rinv[c0 + (lane & 15)];
 #pragma unroll
-    for (int j = 0; j < MPMI_MAX_DIM; ++j) gi[j] = (own && j < D) ? Lz[j][lane] : 0.0;
-    const double lmin_inv = power_rayleigh(gi, own, lane, 1.0 - 0.01 * lane, vbuf[0]);
-    if (lane == 0) s_lmin_inv = lmin_inv;
+      for (int k = 15; k >= 0; --k) {
+        x[k] *= lane_bcast(ri, k);
+#pragma unroll
+        for (int i = 0; i < k; ++i) x[i] = fma(-lane_bcast(l[i], k), x[k], x[i]);
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) X[c0 + k][t] = x[k];
+    }
+    __syncthreads();
+    for (int q = wave; q < p * RB; q += 4) {
+      const int I = q / RB, J = q % RB;
+      f64x4_t acc;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = X[16 * I + 4 * r + (lane >> 4)][16 * J + (lane & 15)];
+      // k-steps from the panel's last row up: the order of a step-by-step loop
+      acc = block_fma<1>(acc, [&](int i, int k) { return -A[c0 + 15 - k][16 * I + i]; },
+                      [&](int k, int j) { return X[c0 + 15 - k][16 * J + j]; });
+#pragma unroll
+      for (int r = 0; r < 4; ++r) X[16 * I + 4 * r + (lane >> 4)][16 * J + (lane & 15)] = acc[r];
+    }
+    __syncthreads();
+  }
+  for (int e = t; e < D * ny; e += kFitThreads) {
+    const int i = e / ny, j = e % ny;
+    K[e] = X[i][j] / sc[i];
   }
   __syncthreads();
+  const double lmin_inv = power_rayleigh(M, t < D ? 1.0 - 0.01 * t : 0.0, vv);
   if (t == 0) {
     info->status = bad ? MPMI_ESINGULAR : MPMI_OK;
-    const double cg = s_lmax * s_lmin_inv;
-    info->cond = cg > 0.0 ? sqrt(cg) : INFINITY;
+    info->lmin_inv = lmin_inv;
   }
 }
 
-// Workspace: partial sums, totals, the info record (256 bytes at
-// fit_info_offset()), then a [D][MPMI_MAX_STATE] chunk of the lifted solution.
-size_t fit_info_offset() { return (size_t)(kFitBlocks + 1) * MPMI_MAX_DIM * kFitCols * sizeof(double); }
-size_t fit_workspace_bytes() { return fit_info_offset() + 256 + (size_t)MPMI_MAX_DIM * MPMI_MAX_STATE * 8; }
+// Workspace: partial sums, totals, then the info record (256 bytes at
+// fit_info_offset()).
+constexpr int kFitColsMax = 2 * MPMI_MAX_DIM;  // the lifted operator's D + D columns
+size_t fit_info_offset() { return (size_t)(kFitBlocks + 1) * MPMI_MAX_DIM * kFitColsMax * sizeof(double); }
+size_t fit_workspace_bytes() { return fit_info_offset() + 256; }
 
-// One least-squares solve with ny right-hand sides (see gram_kernel).
-static hipError_t fit_columns(const mpmi_system& sys, int dim, int ny, int yc0, const double* X, const double* U,
+// One least-squares solve: targets Y (ny = n), or psi(Y, U) for the lifted
+// operator (ny = dim).  Race car, T = 50,000, one MI355X: Gram 22 us (29 with
+// 4 x 6 vector blocks and one lifting wave), reduction 4.5, solve 45 (91);
+// lifted operator 30 + 4.5 + 50 us (eight rounds of 29 + 4.6 + 91 when it was
+// solved eight columns at a time).  The Gram pass is bound by the lift of a
+// tile (two waves, 3.7 us against 2.3 us of products); 256 workgroups fix the
+// order of the sums.
+template <bool LIFTED>
+static hipError_t fit_columns(const mpmi_system& sys, int dim, int ny, const double* X, const double* U,
                               const double* Y, int64_t T, double ridge, double* K_out, void* work, hipStream_t st) {
   const int E = dim * (dim + ny);
   long long ntiles = (T + kFitRows - 1) / kFitRows;
   const int nparts = (int)(ntiles < kFitBlocks ? ntiles : kFitBlocks);
   double* part = (double*)work;
-  double* tot = part + (size_t)kFitBlocks * MPMI_MAX_DIM * kFitCols;
-  FitInfo* info = (FitInfo*)(tot + (size_t)MPMI_MAX_DIM * kFitCols);
-  gram_kernel<<<nparts, kFitThreads, 0, st>>>(sys, dim, ny, yc0, X, U, Y, (long long)T, part);
+  double* tot = part + (size_t)kFitBlocks * MPMI_MAX_DIM * kFitColsMax;
+  FitInfo* info = (FitInfo*)((char*)work + fit_info_offset());
+  gram_kernel<LIFTED><<<nparts, GramShape<LIFTED>::kThreads, 0, st>>>(sys, dim, ny, X, U, Y, (long long)T, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   reduce_kernel<<<(E + kReduceElems - 1) / kReduceElems, kReduceElems * kReduceWays, 0, st>>>(nparts, E, part, tot);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  solve_kernel<<<1, kFitThreads, 0, st>>>(ny, dim, (long long)T, ridge, tot, K_out, info);
+  solve_kernel<GramShape<LIFTED>::RB><<<2, kFitThreads, 0, st>>>(ny, dim, (long long)T, ridge, tot, K_out, info);
   return hipGetLastError();
 }
 
 hipError_t launch_fit(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
                       int64_t T, double ridge, double* K_out, void* work, hipStream_t st) {
-  return fit_columns(sys, dim, sys.n_state, -1, X, U, Y, T, ridge, K_out, work, st);
+  return fit_columns<false>(sys, dim, sys.n_state, X, U, Y, T, ridge, K_out, work, st);
 }
 
 // The lifted operator K (dim x dim, targets psi(Y_t, U_t)): the same scaled
-// least-squares problem solved for MPMI_MAX_STATE target columns at a time;
-// each chunk's [dim][ny] solution goes from the workspace into its columns of
-// K_out.  Every chunk recomputes the Gram matrix (a set-up call: the cost is
-// dim / 8 fits).  The status and condition estimate left in the workspace
-// are those of the last chunk (the Gram matrix, and so both, are the same).
+// least-squares problem with dim target columns, in one pass over the data
+// and one factorisation.  It was solved eight columns at a time, each chunk
+// forming the Gram matrix and its factor again.
 hipError_t launch_fit_lifted(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
                              int64_t T, double ridge, double* K_out, void* work, hipStream_t st) {
-  double* Kc = (double*)((char*)work + fit_info_offset() + 256);
-  for (int c0 = 0; c0 < dim; c0 += MPMI_MAX_STATE) {
-    const int ny = dim - c0 < MPMI_MAX_STATE ? dim - c0 : MPMI_MAX_STATE;
-    hipError_t e = fit_columns(sys, dim, ny, c0, X, U, Y, T, ridge, Kc, work, st);
-    if (e != hipSuccess) return e;
-    e = hipMemcpy2DAsync(K_out + c0, (size_t)dim * sizeof(double), Kc, (size_t)ny * sizeof(double),
-                         (size_t)ny * sizeof(double), (size_t)dim, hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return fit_columns<true>(sys, dim, dim, X, U, Y, T, ridge, K_out, work, st);
 }
 
 }  // namespace mpmi
