@@ -103,9 +103,8 @@ enum { MPMI_ATOM_ONE = 0, MPMI_ATOM_VAR = 1, MPMI_ATOM_SIN = 2, MPMI_ATOM_COS = 
  *          their FP32 verdicts.  With bands at least the
  *          FP32 rollout's margin error, the selection is that of an FP64
  *          rollout, and so is every first violation outside the band (and
- *          every one, when nothing is safe).  One lane per candidate in the
- *          FP32 tick; ticks of at most 2^22 candidates (MPMI_EUNSUPPORTED
- *          otherwise);
+ *          every one, when nothing is safe).  lanes_per_cand 0 or 1; ticks of
+ *          at most 2^22 candidates (MPMI_EUNSUPPORTED otherwise);
  *          trajectories, when stored, are the FP32 states.
  *  BF16X3  the contraction runs on BF16 matrix cores as three products of
  *          hi/lo BF16 splits of the features and of (K - E) in residual form
@@ -229,10 +228,11 @@ typedef struct mpmi_tick_desc {
   int32_t horizon;        /* H, 1..255 */
   int32_t precision;      /* MPMI_PREC_* */
   int32_t block;          /* threads per workgroup: 0 (library default) or 64..1024, multiple of 64 */
-  int32_t lanes_per_cand; /* FP32 ticks: 0 or 1 (one lane per candidate), or 2 / 4 / 8 lanes per
-                             candidate, each lane computing a share of the state (lower latency at
-                             small N; block <= 256); the same operations in the same order as one
-                             lane, so the same selection */
+  int32_t lanes_per_cand; /* FP32 ticks: 0 (the library chooses by basis and N), 1 (one lane per
+                             candidate), or 2 / 4 / 8 lanes per candidate, each lane computing a
+                             share of the state (lower latency at small N; block <= 256); the same
+                             operations in the same order as one lane, so the same selection.
+                             FP32_RECHECK64 and custom-basis ticks: 0 or 1, the library chooses */
 } mpmi_tick_desc;
 
 typedef struct mpmi_ctx_s* mpmi_ctx;
@@ -673,7 +673,7 @@ mpmi_status mdn_sample(mpmi_ctx ctx, const void* model, const float* head, int32
  * tick described by *fallback (GRID or UNIFORM), which runs only if *out
  * holds MPMI_NO_SAFE and then overwrites it (out->n_cand tells which
  * candidate set decided).  Each of the two ticks is FP32 or FP32_RECHECK64
- * (its descriptor's precision; the latter with one lane per candidate and at
+ * (its descriptor's precision; the latter with lanes_per_cand 0 or 1 and at
  * most 2^22 candidates, and sharing the context's recheck list, so ordered
  * on one stream with the context's other such ticks).  cand_work [1][2][P]
  * device; head_out [80] device or NULL; w_bf16 16-byte aligned (MPMI_EINVAL

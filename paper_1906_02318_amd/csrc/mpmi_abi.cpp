@@ -579,6 +579,67 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
   return MPMI_OK;
 }
 
+// Lanes per candidate of an FP32 or FP32_RECHECK64 tick.  `open`: the descriptor
+// leaves the choice to the library (results do not depend on it, every form
+// giving the same bits); the forms of several lanes serve the bases with a
+// split kernel, noise-free models and workgroups of up to 256, and store no
+// trajectories.
+//
+// Up to 65,536 lanes are one wave per SIMD of the chip, whose step takes the
+// longer the more columns a lane forms: the most lanes that fit win, to 8.
+// Race car, H = 60, us by lanes 1 / 2 / 4 / 8: 8,193 candidates 76 / 35 / 31.5 /
+// 30; 12,289 75 / 35 / 33 / 37; 16,385 76 / 36 / 38 / 41; 32,769 75 / 37 / 42 /
+// 55.  Past that a second wave per SIMD makes two lanes slower at once (49,153:
+// 71), while three waves of the four-lane form still beat one lane (61 against
+// 76); 65,537: 78 / 97 / 81 / 102.  (FP32_RECHECK64 adds its two launches to
+// each.)  The balance bot's step is short and the publication of a workgroup
+// (15 ns each) weighs more than its columns: H = 50, 4,097 candidates 31 / 17.3 /
+// 16.7 / 18.6; 16,385 31 / 18.8 / 20 / 23; 262,145 49 / 46 / 75 / 166.  A custom
+// basis has one split form, of eight lanes (three-input car, H = 25: 10,121
+// candidates 159 / 28.6; 60,001 162 / 80; 120,001 174 / 136; level near 155,000).
+static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj, bool open) {
+  if (d.lanes_per_cand > 1) return d.lanes_per_cand;
+  if (!open || traj || d.block > 256 || mpmi::system_noisy(sys)) return 1;
+  const long long c = (long long)d.n_cand + 1;
+  switch (sys.basis) {
+    case MPMI_BASIS_BALANCE_BOT:
+      return c <= 4096 + 1 ? 4 : (c <= 262144 + 1 ? 2 : 1);
+    case MPMI_BASIS_RACE_CAR:
+      if (8 * c <= 65536) return 8;
+      if (4 * c <= 65536) return 4;
+      if (2 * c <= 65536 + 64) return 2;  // 32,768 points and the user's input
+      return 4 * c <= 3 * 65536 ? 4 : 1;
+    case MPMI_BASIS_CUSTOM:
+      return c <= 131072 + 1 ? 8 : 1;
+    default:
+      return 1;
+  }
+}
+
+// lanes_per_cand 1 asks for the one-lane form of an FP32 tick of a fixed basis;
+// FP32_RECHECK64 and custom-basis ticks take no value past it, so 1 leaves the
+// choice open there too (the autotuner sets it).
+static bool lanes_open(const mpmi_system& sys, const mpmi_tick_desc& d) {
+  return d.lanes_per_cand == 0 || d.precision == MPMI_PREC_FP32_RECHECK64 || sys.basis == MPMI_BASIS_CUSTOM;
+}
+
+// One FP32 or FP32_RECHECK64 tick (recheck list `rl` of `capacity` entries for
+// the latter) in the form the descriptor or tick_lanes names.
+static hipError_t run_tick(const mpmi_system& sys, const void* model, const mpmi_tick_desc& d, bool open,
+                           const float* x_t, const float* u_user, const float* cand, void* slot, mpmi_selection* out, int16_t* fv,
+                           float* traj, long long traj_ld, void* rl, int capacity, hipStream_t st,
+                           const mpmi_selection* gate = nullptr) {
+  const bool r64 = d.precision == MPMI_PREC_FP32_RECHECK64;
+  void* const list = r64 ? rl : nullptr;
+  const int grid = r64 ? mpmi::device_cu_count() * 4 : 0;
+  const int lanes = tick_lanes(sys, d, traj != nullptr, open);
+  if (lanes > 1)
+    return mpmi::launch_tick_split(sys, lanes, model, d, x_t, u_user, cand, slot, out, fv, st, gate, list, capacity,
+                                   grid);
+  return mpmi::launch_tick(sys, model, d, x_t, u_user, cand, slot, out, fv, traj, traj_ld, st, gate, list, capacity,
+                           grid);
+}
+
 mpmi_status mpmi_tick(mpmi_ctx ctx, const void* model, const mpmi_tick_desc* desc, const float* x_t,
                       const float* u_user, const float* cand, mpmi_selection* out, int16_t* first_violation,
                       float* traj, int64_t traj_ld, void* stream) {
@@ -599,9 +660,6 @@ mpmi_status mpmi_tick(mpmi_ctx ctx, const void* model, const mpmi_tick_desc* des
     if (desc->block > 256) return fail(ctx, MPMI_EUNSUPPORTED, "several lanes per candidate: block <= 256");
     if (mpmi::system_noisy(sys))
       return fail(ctx, MPMI_EUNSUPPORTED, "several lanes per candidate: noise-free models only");
-    return check_hip(ctx, mpmi::launch_tick_split(sys, desc->lanes_per_cand, model, *desc, x_t, u_user, cand,
-                                                  slot, out, first_violation, (hipStream_t)stream),
-                     "mpmi_tick (split) launch");
   }
   if (desc->precision == MPMI_PREC_BF16X3) {
     if (sys.basis != MPMI_BASIS_RACE_CAR)
@@ -624,13 +682,9 @@ mpmi_status mpmi_tick(mpmi_ctx ctx, const void* model, const mpmi_tick_desc* des
       return fail(ctx, MPMI_EUNSUPPORTED,
                   "FP32_RECHECK64 ticks take at most %d candidates (the FP64 recheck list holds every one)",
                   mpmi::kRecheckCapacity);
-    return check_hip(ctx, mpmi::launch_tick(sys, model, *desc, x_t, u_user, cand, slot, out, first_violation, traj,
-                                            traj ? traj_ld : 0, (hipStream_t)stream, nullptr, ctx->recheck,
-                                            mpmi::kRecheckCapacity, mpmi::device_cu_count() * 4),
-                     "mpmi_tick (FP32_RECHECK64) launch");
   }
-  return check_hip(ctx, mpmi::launch_tick(sys, model, *desc, x_t, u_user, cand, slot, out, first_violation,
-                                          traj, traj ? traj_ld : 0, (hipStream_t)stream),
+  return check_hip(ctx, run_tick(sys, model, *desc, lanes_open(sys, *desc), x_t, u_user, cand, slot, out, first_violation, traj,
+                                 traj ? traj_ld : 0, ctx->recheck, mpmi::kRecheckCapacity, (hipStream_t)stream),
                    "mpmi_tick launch");
 }
 
@@ -1053,22 +1107,15 @@ mpmi_status mpmi_proposal_tick(mpmi_ctx ctx, const void* model, const uint16_t* 
                                               model, pd.n_cand, pd.seed, pd.tick, pd.loop, cand_work, st);
   void* slot = (char*)ctx->slots + (size_t)pd.loop * mpmi::slot_bytes();
   if (e == hipSuccess) {
-    if (pd.lanes_per_cand > 1)
-      e = mpmi::launch_tick_split(sys, pd.lanes_per_cand, model, pd, x_t, u_user, cand_work, slot, out, nullptr,
-                                  st);
-    else if (r64)
-      e = mpmi::launch_tick(sys, model, pd, x_t, u_user, cand_work, slot, out, nullptr, nullptr, 0, st, nullptr,
-                            ctx->recheck, mpmi::kRecheckCapacity, mpmi::device_cu_count() * 4);
-    else
-      e = mpmi::launch_tick(sys, model, pd, x_t, u_user, cand_work, slot, out, nullptr, nullptr, 0, st);
+    e = run_tick(sys, model, pd, true, x_t, u_user, cand_work, slot, out, nullptr, nullptr, 0, ctx->recheck,
+                 mpmi::kRecheckCapacity, st);
   }
   void* slot2 = (char*)ctx->slots + (size_t)fallback->loop * mpmi::slot_bytes();
   if (e == hipSuccess) {
-    if (fb64)
-      e = mpmi::launch_tick(sys, model, *fallback, x_t, u_user, nullptr, slot2, out, nullptr, nullptr, 0, st, out,
-                            ctx->recheck, mpmi::kRecheckCapacity, mpmi::device_cu_count() * 4);
-    else
-      e = mpmi::launch_tick(sys, model, *fallback, x_t, u_user, nullptr, slot2, out, nullptr, nullptr, 0, st, out);
+    mpmi_tick_desc fd = *fallback;
+    fd.lanes_per_cand = 0;
+    e = run_tick(sys, model, fd, true, x_t, u_user, nullptr, slot2, out, nullptr, nullptr, 0, ctx->recheck,
+                 mpmi::kRecheckCapacity, st, out);
   }
   return check_hip(ctx, e, "mpmi_proposal_tick launch");
 }
@@ -1193,15 +1240,8 @@ extern "C" mpmi_status mpmi_tick_noalloc(const mpmi_system* sys, const void* mod
   void* slot = (char*)base + (size_t)desc->loop * sizeof(mpmi::Slot);
   void* list = (char*)base + offsetof(ScratchImage, count);
   const hipStream_t st = (hipStream_t)stream;
-  hipError_t e;
-  if (desc->lanes_per_cand > 1)
-    e = mpmi::launch_tick_split(*sys, desc->lanes_per_cand, model, *desc, x_t, u_user, cand, slot, out,
-                                first_violation, st);
-  else if (desc->precision == MPMI_PREC_FP32_RECHECK64)
-    e = mpmi::launch_tick(*sys, model, *desc, x_t, u_user, cand, slot, out, first_violation, nullptr, 0, st, nullptr,
-                          list, kScratchRecheck, mpmi::device_cu_count() * 4);
-  else
-    e = mpmi::launch_tick(*sys, model, *desc, x_t, u_user, cand, slot, out, first_violation, nullptr, 0, st);
+  const hipError_t e = run_tick(*sys, model, *desc, lanes_open(*sys, *desc), x_t, u_user, cand, slot, out,
+                                first_violation, nullptr, 0, list, kScratchRecheck, st);
   if (e != hipSuccess) return fail(nullptr, MPMI_EDEVICE, "mpmi_tick_noalloc launch: %s", hipGetErrorString(e));
   g_noctx_err.clear();
   return MPMI_OK;

@@ -103,10 +103,13 @@ hipError_t launch_tick_lifted(const mpmi_system& sys, void* lifted, int h_max, c
                               mpmi_selection* out, int16_t* fv, float* traj, long long traj_ld, int grid_per_cu,
                               hipStream_t st);
 
-// Latency form of the tick (mpmi_split.hip).
+// Latency form of the tick (mpmi_split.hip): `split` lanes per candidate (2, 4
+// or 8; 8 for a custom basis), noise-free models, no trajectories.  `gate`
+// and `recheck` as in launch_tick.
 hipError_t launch_tick_split(const mpmi_system& sys, int split, const void* model, const mpmi_tick_desc& d,
                              const float* x_t, const float* u_user, const float* cand, void* slot,
-                             mpmi_selection* out, int16_t* fv, hipStream_t st);
+                             mpmi_selection* out, int16_t* fv, hipStream_t st, const mpmi_selection* gate,
+                             void* recheck, int recheck_capacity, int recheck_grid);
 
 // BF16X3 race-car tick + FP32 recheck (mpmi_bf16.hip).
 constexpr int kRecheckCapacity = 1 << 22;

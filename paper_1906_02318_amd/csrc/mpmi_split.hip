@@ -7,9 +7,11 @@
 // (J = ceil(n / SPLIT)) from the full feature set, and the group rebuilds the
 // full next state with cross-lane permutes, so each lane's contraction is
 // J / n of the one-lane form, at the price of redundant feature and safety
-// work.  The autotuner picks SPLIT (1, 2, 4 or 8) and the workgroup size per
-// workload.
+// work.  The caller, the autotuner or the library (tick_lanes, by candidate
+// count) picks SPLIT.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "mpmi_device.hpp"
 #include "mpmi_launch.hpp"
@@ -150,53 +152,75 @@ struct SplitRows {
 // the model's has_track flag, fixed per kernel instance; the float constants
 // are pinned to vector registers (the scalar file is too small to hold them
 // beside the loop's own state).
-template <int NS, int DEG, bool TRACK>
+//
+// NEAR (FP32_RECHECK64): check() also ORs into *near whether some margin lies
+// within its constraint's FP32 band, as min_margin_near does.
+template <int NS, int DEG, bool TRACK, bool NEAR = false>
 struct SafetyRegs {
   float lim[NS], p[DEG + 1], q[DEG], trk_lim;
+  float eps[NEAR ? NS : 1], trk_eps;
   bool chk[NS];
   __device__ __forceinline__ void load(const ModelDev* __restrict__ md) {
+    // Every constant is loaded before the first is pinned: a pin waits.
     const ConstSafety* sc = (const ConstSafety*)(uintptr_t)&md->safe;
     const int mask = sc->comp_mask;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
       chk[k] = (mask >> k) & 1;
       lim[k] = sc->comp_lim[k];
-      asm volatile("" : "+v"(lim[k]));
+      if constexpr (NEAR) eps[k] = sc->comp_eps[k];
     }
     if constexpr (TRACK) {
       trk_lim = sc->trk_lim;
+      if constexpr (NEAR) trk_eps = sc->trk_eps;
+#pragma unroll
+      for (int k = 0; k <= DEG; ++k) p[k] = sc->trk_p[k];
+#pragma unroll
+      for (int k = 0; k < DEG; ++k) q[k] = sc->trk_q[k];
+    }
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      asm volatile("" : "+v"(lim[k]));
+      if constexpr (NEAR) {
+        eps[k] = chk[k] ? eps[k] : 0.0f;  // |margin| < 0 is never true
+        asm volatile("" : "+v"(eps[k]));
+      }
+    }
+    if constexpr (TRACK) {
       asm volatile("" : "+v"(trk_lim));
+      if constexpr (NEAR) asm volatile("" : "+v"(trk_eps));
 #pragma unroll
-      for (int k = 0; k <= DEG; ++k) {
-        p[k] = sc->trk_p[k];
-        asm volatile("" : "+v"(p[k]));
-      }
+      for (int k = 0; k <= DEG; ++k) asm volatile("" : "+v"(p[k]));
 #pragma unroll
-      for (int k = 0; k < DEG; ++k) {
-        q[k] = sc->trk_q[k];
-        asm volatile("" : "+v"(q[k]));
-      }
+      for (int k = 0; k < DEG; ++k) asm volatile("" : "+v"(q[k]));
     }
   }
   // Bitwise, not short-circuit, combination: each test is one compare into a
   // lane mask, with no branch.
-  __device__ __forceinline__ bool safe(const float* x) const {
+  __device__ __forceinline__ bool track(float x0, float x1, bool* near) const {
+    if constexpr (!TRACK) return true;
+    const float r2 = fmaf(x0, x0, x1 * x1);
+    const float inv = __builtin_amdgcn_rsqf(r2);
+    const float rho = r2 * inv;
+    const float c1 = x0 * inv, s1 = x1 * inv;
+    float P = p[DEG];
+#pragma unroll
+    for (int k = DEG - 1; k >= 0; --k) P = fmaf(P, c1, p[k]);
+    float Q = q[DEG - 1];
+#pragma unroll
+    for (int k = DEG - 2; k >= 0; --k) Q = fmaf(Q, c1, q[k]);
+    const float off = fabsf(rho - fmaf(s1, Q, P));
+    if constexpr (NEAR) *near |= fabsf(trk_lim - off) < trk_eps;
+    return off < trk_lim;
+  }
+  __device__ __forceinline__ bool safe(const float* x, bool* near) const {
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < NS; ++k) ok &= (fabsf(x[k]) < lim[k]) | !chk[k];
-    if constexpr (TRACK) {
-      const float r2 = fmaf(x[0], x[0], x[1] * x[1]);
-      const float inv = __builtin_amdgcn_rsqf(r2);
-      const float rho = r2 * inv;
-      const float c1 = x[0] * inv, s1 = x[1] * inv;
-      float P = p[DEG];
+    if constexpr (NEAR)
 #pragma unroll
-      for (int k = DEG - 1; k >= 0; --k) P = fmaf(P, c1, p[k]);
-      float Q = q[DEG - 1];
-#pragma unroll
-      for (int k = DEG - 2; k >= 0; --k) Q = fmaf(Q, c1, q[k]);
-      ok &= fabsf(rho - fmaf(s1, Q, P)) < trk_lim;
-    }
+      for (int k = 0; k < NS; ++k) *near |= fabsf(lim[k] - fabsf(x[k])) < eps[k];
+    if constexpr (TRACK) ok &= track(x[0], x[1], near);
     return ok;
   }
 };
@@ -229,15 +253,45 @@ __device__ __forceinline__ void rebuild_state(const float* y, float* x) {
   }
 }
 
-template <int BASIS, int SPLIT, int DEG, bool TRACK>
+// The end of a latency-form tick, every thread of the workgroup calling it:
+// lead lanes (one per candidate) hold fv and the cost.  RECHECK: near-band
+// candidates go to the list with their FP32 verdict instead of publishing, as
+// in tick_fp32_kernel, and the launches that follow complete the slot.
+template <int MS, bool RECHECK>
+__device__ __forceinline__ void split_finish(const ModelDev* __restrict__ md, const GenParams& gp, int H,
+                                             const float* __restrict__ u_user, const float* __restrict__ cand,
+                                             Slot* __restrict__ slot, mpmi_selection* __restrict__ out,
+                                             RecheckList* __restrict__ rl, bool lead, bool near, int c, int fv,
+                                             float cst) {
+  const bool listed = RECHECK && lead && near;
+  const bool pub = lead && !listed;
+  const bool safe = pub && fv == H + 1;
+  const unsigned long long ks = safe ? safe_key(cst, c) : kKeyNone;
+  const unsigned long long kf = (pub && !safe) ? fallback_key(fv, cst, c) : kKeyNone;
+  if constexpr (RECHECK) {
+    wave_append(&rl->count, rl->idx, listed, (c << 1) | (fv == H + 1 ? 1 : 0));
+    publish_partial(ks, kf, (unsigned int)__popcll(__ballot(safe && c > 0)), (unsigned int)__popcll(__ballot(listed)),
+                    slot, blockIdx.x);
+  } else {
+    if (reduce_and_publish(ks, kf, safe && c > 0, slot, gridDim.x, blockIdx.x) && threadIdx.x == 0)
+      finalize<MS>(md, gp, cand, u_user, H, slot, out);
+  }
+}
+
+// GATED (the fallback after a proposal tick): nothing to do if the gate
+// selection already found a safe candidate; an instance of its own, since the
+// test would hold up the other loads of every launch.
+template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED>
 __global__ void __launch_bounds__(256)
 tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
                   const float* __restrict__ u_user, const float* __restrict__ cand, Slot* __restrict__ slot,
-                  mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out) {
+                  mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out, RecheckList* __restrict__ rl,
+                  const mpmi_selection* __restrict__ gate) {
   constexpr int NS = Dims<BASIS>::N, MS = Dims<BASIS>::M;
   constexpr int J = (NS + SPLIT - 1) / SPLIT;
   constexpr int D = (BASIS == MPMI_BASIS_RACE_CAR) ? 64 : 21;
   static_assert(SPLIT == 2 || SPLIT == 4 || SPLIT == 8, "groups of 2, 4 or 8 lanes (one row half)");
+  if (GATED && gate->status == MPMI_OK) return;
   __shared__ __attribute__((aligned(16))) float sK8[kSplitRows * 8];
   // A group never straddles a quad (2, 4) or a row half (8): the launch
   // uses a block that is a multiple of 64, so lane l of a wave holds gid with
@@ -262,7 +316,7 @@ tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const fl
   F.fold(sK8, colpos, u);
   SplitRows<BASIS, J> Kr;
   Kr.load(sK8, D, colpos);
-  SafetyRegs<NS, DEG, TRACK> sr;
+  SafetyRegs<NS, DEG, TRACK, RECHECK> sr;
   sr.load(md);
   // The cost needs only the first segment's input: taken now, so its loads
   // are not on the path after the horizon.
@@ -272,6 +326,7 @@ tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const fl
   // carries no wait for them.
   __syncthreads();
   int fv = H + 1;
+  bool near = false;
   if (valid) {
     const int S = gp.n_seg;
     // Segment g covers steps s with floor((s - 1) S / H) == g; the next
@@ -334,67 +389,290 @@ tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const fl
       // operations), so they leave the loop at the same step.
       rebuild_state<NS, J, SPLIT>(y, x);
       settle_state<NS>(x);
-      if (!sr.safe(x)) {
+      if (!sr.safe(x, &near)) {
         fv = s;
         break;
       }
     }
     if (fv_out && h == 0) fv_out[c] = (int16_t)fv;
   }
-  const bool safe = lead && fv == H + 1;
-  const unsigned long long ks = safe ? safe_key(cst, c) : kKeyNone;
-  const unsigned long long kf = (lead && !safe) ? fallback_key(fv, cst, c) : kKeyNone;
-  if (reduce_and_publish(ks, kf, safe && c > 0, slot, gridDim.x, blockIdx.x) && threadIdx.x == 0)
-    finalize<MS>(md, gp, cand, u_user, H, slot, out);
+  split_finish<MS, RECHECK>(md, gp, H, u_user, cand, slot, out, rl, lead, near, c, fv, cst);
 }
 
-template <int BASIS, int DEG, bool TRACK>
-static void split_dispatch(int split, unsigned grid, int block, hipStream_t st, const ModelDev* md, const GenParams& gp,
-                           int H, const float* x_t, const float* u_user, const float* cand, Slot* sl,
-                           mpmi_selection* out, int16_t* fv) {
-  if (split == 2)
-    tick_split_kernel<BASIS, 2, DEG, TRACK><<<grid, block, 0, st>>>(md, gp, H, x_t, u_user, cand, sl, out, fv);
-  else if (split == 4)
-    tick_split_kernel<BASIS, 4, DEG, TRACK><<<grid, block, 0, st>>>(md, gp, H, x_t, u_user, cand, sl, out, fv);
-  else
-    tick_split_kernel<BASIS, 8, DEG, TRACK><<<grid, block, 0, st>>>(md, gp, H, x_t, u_user, cand, sl, out, fv);
+// Latency form for a basis given as data: one candidate over the 8 lanes of an
+// aligned lane group.  Per step the group evaluates its atoms (lane h atoms h,
+// h + 8, ...) into its row of an LDS table, lane h forms the products of
+// features 8 h .. 8 h + 7 (their two row offsets in registers), and every
+// lane sums all the products, taken from the lanes that hold them by DPP, times
+// column h of K, which it holds in registers for the whole horizon.  A wave's
+// LDS operations execute in order, so the exchanges need no wait or barrier,
+// only the compiler kept from moving them.  Atoms, products and the sum over
+// features take the one-lane step's operations in its order: the same bits.
+// The one-lane step reads every feature's two atom numbers by dependent scalar
+// loads and runs a latency-bound wave at 6.3 us per step (three-input car, 64
+// features, 10,121 candidates, 25 steps: 159 us); here 0.7
+// us per step, 28.6 us.  Exchanging the products through LDS instead of DPP took
+// 38 us, as did the same with the verdict after the step instead of beside the
+// next one.
+constexpr int kCustomGroup = 8;
+constexpr int kCustomW = 12;                    // x (8), u (4)
+constexpr int kCustomAt = MPMI_MAX_ATOMS + 1;   // row strides that spread the groups over the banks
+static_assert(MPMI_MAX_STATE == kCustomGroup && MPMI_MAX_DIM == 8 * kCustomGroup, "one column and eight features per lane");
+
+// The eight products v[] of lane L of each quad, in order, times k[], added to
+// y: v_fmac_f32 with its first operand taken from that lane by DPP (one rounding
+// per feature, as fmaf).  In one statement, with the two wait states a DPP read
+// needs after the instruction that wrote its operand.
+template <int L>
+__device__ __forceinline__ float add_eight(const float (&v)[8], const float* k, float y) {
+#define MPMI_FMAC(i, j) "v_fmac_f32_dpp %0, %" #i ", %" #j " quad_perm:[%c17,%c17,%c17,%c17] row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_nop 1\n\t" MPMI_FMAC(1, 9) MPMI_FMAC(2, 10) MPMI_FMAC(3, 11) MPMI_FMAC(4, 12) MPMI_FMAC(5, 13)
+          MPMI_FMAC(6, 14) MPMI_FMAC(7, 15) MPMI_FMAC(8, 16) "s_nop 0"
+      : "+v"(y)
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]), "v"(k[0]), "v"(k[1]),
+        "v"(k[2]), "v"(k[3]), "v"(k[4]), "v"(k[5]), "v"(k[6]), "v"(k[7]), "i"(L));
+#undef MPMI_FMAC
+  return y;
+}
+
+template <bool TRACK, bool RECHECK>
+__global__ void __launch_bounds__(256)
+tick_custom_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
+                         const float* __restrict__ u_user, const float* __restrict__ cand, Slot* __restrict__ slot,
+                         mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out,
+                         RecheckList* __restrict__ rl) {
+  constexpr int NS = MPMI_MAX_STATE, MS = MPMI_MAX_INPUT, kGroups = 256 / kCustomGroup;
+  __shared__ float sW[kGroups][kCustomW];
+  __shared__ float sAt[kGroups][kCustomAt];
+  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
+  const int c = gid / kCustomGroup, h = gid % kCustomGroup, row = threadIdx.x / kCustomGroup;
+  const bool valid = c < gp.n_cand + 1;
+  const int n = md->n, m = md->m, D = md->dim, na = md->sys.n_atoms;
+  float u0[MS];
+#pragma unroll
+  for (int j = 0; j < MS; ++j) u0[j] = (valid && j < m) ? cand_value(gp, md, cand, u_user, c, 0, j) : 0.0f;
+  sW[row][h] = h < n ? x_t[h] : 0.0f;
+  if (h < MS) {
+    float v = u0[0];
+#pragma unroll
+    for (int j = 1; j < MS; ++j) v = h == j ? u0[j] : v;
+    sW[row][NS + h] = v;
+  }
+  float kcol[MPMI_MAX_DIM];
+#pragma unroll
+  for (int f = 0; f < MPMI_MAX_DIM; ++f) kcol[f] = md->K[f][h];
+  // Atom rows of this lane's features (one past the last feature: the row's
+  // zero entry, so its product adds 0 * 0) and its atoms' kinds and variables.
+  int fa[8], fb[8], kind[4], var[4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    fa[i] = 8 * h + i < D ? md->sys.feat_a[8 * h + i] : MPMI_MAX_ATOMS;
+    fb[i] = 8 * h + i < D ? md->sys.feat_b[8 * h + i] : MPMI_MAX_ATOMS;
+  }
+  if (h == 0) sAt[row][MPMI_MAX_ATOMS] = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int q = h + 8 * i;
+    kind[i] = q < na ? md->sys.atom_kind[q] : MPMI_ATOM_ONE;
+    const int v = q < na ? md->sys.atom_var[q] : 0;
+    var[i] = v < n ? v : NS + (v - n);
+  }
+  SafetyRegs<NS, kMaxHarm, TRACK, RECHECK> sr;
+  sr.load(md);
+  // This lane's own box (the others' limits are dead after this).
+  float lim = sr.lim[0], eps = RECHECK ? sr.eps[0] : 0.0f;
+  bool boxed = sr.chk[0];
+#pragma unroll
+  for (int k = 1; k < NS; ++k) {
+    lim = h == k ? sr.lim[k] : lim;
+    boxed = h == k ? sr.chk[k] : boxed;
+    if (RECHECK) eps = h == k ? sr.eps[k] : eps;
+  }
+  const bool lead = valid && h == 0;
+  const float cst = lead ? cost_of<MS>(md, u0, u_user) : 0.0f;
+  const int base = threadIdx.x & 63 & ~(kCustomGroup - 1);
+  __syncthreads();
+  int fv = H + 1;
+  bool near = false;
+  if (valid) {
+    const int S = gp.n_seg;
+    int nxt = (H + S - 1) / S;
+    float own = 0.0f;  // component h of the state being checked
+    for (int s = 1; s <= H; ++s) {
+      if (s - 1 >= nxt) {
+        const int g = ((s - 1) * S) / H;
+        nxt = ((g + 1) * H + S - 1) / S;
+        if (h < m) sW[row][NS + h] = cand_value(gp, md, cand, u_user, c, g, h);
+        asm volatile("" ::: "memory");
+      }
+      // This lane's atoms, all read before the first is evaluated; the second
+      // half only for more than 16 atoms (entries past the last are not read).
+      auto atoms = [&](auto first) {
+        constexpr int i0 = decltype(first)::value;
+        const float w0 = sW[row][var[i0]], w1 = sW[row][var[i0 + 1]];
+        const float w[2] = {w0, w1};
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float sn = __sinf(w[i]), cs = __cosf(w[i]);
+          float a = 1.0f;
+          a = kind[i0 + i] == MPMI_ATOM_VAR ? w[i] : a;
+          a = kind[i0 + i] == MPMI_ATOM_SIN ? sn : a;
+          a = kind[i0 + i] == MPMI_ATOM_COS ? cs : a;
+          sAt[row][h + 8 * (i0 + i)] = a;
+        }
+      };
+      atoms(std::integral_constant<int, 0>{});
+      if (na > 16) atoms(std::integral_constant<int, 2>{});  // uniform
+      asm volatile("" ::: "memory");
+      float p[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) p[i] = sAt[row][fa[i]] * sAt[row][fb[i]];
+      // The verdict of x_{s-1}, beside the step that forms x_s (the two chains
+      // overlap; an unsafe x_{s-1} ends the rollout and x_s is dropped): lane h
+      // tests component h's box, every lane the track, and one ballot combines
+      // the group's tests (its lanes are all active: they leave the loop
+      // together).  x_0, the current state, is not checked.
+      bool nr = false;
+      if (RECHECK) nr = fabsf(lim - fabsf(own)) < eps;
+      bool ok = (fabsf(own) < lim) | !boxed;
+      ok &= sr.track(group_lane<8, 0>(own), group_lane<8, 1>(own), &nr);
+      // The products of lanes 0 .. 3 of the group in both quads, and those of
+      // lanes 4 .. 7: one DPP move each (row_shr:4 into banks 1 and 3,
+      // row_shl:4 into banks 0 and 2; the other banks keep their own).
+      float pa[8], pb[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int v = __builtin_bit_cast(int, p[i]);
+        pa[i] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xF, 0xA, false));
+        pb[i] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, 0x104, 0xF, 0x5, false));
+      }
+      float y = 0.0f;
+      y = add_eight<0>(pa, kcol, y);
+      y = add_eight<1>(pa, kcol + 8, y);
+      y = add_eight<2>(pa, kcol + 16, y);
+      y = add_eight<3>(pa, kcol + 24, y);
+      if (D > 32) {  // uniform
+        y = add_eight<0>(pb, kcol + 32, y);
+        y = add_eight<1>(pb, kcol + 40, y);
+        y = add_eight<2>(pb, kcol + 48, y);
+        y = add_eight<3>(pb, kcol + 56, y);
+      }
+      y = h < n ? y : 0.0f;
+      sW[row][h] = y;
+      asm volatile("" ::: "memory");
+      const unsigned long long okm = __ballot(ok);
+      if (s > 1) {
+        near |= nr;
+        if (((okm >> base) & 0xFFull) != 0xFFull) {
+          fv = s - 1;
+          break;
+        }
+      }
+      own = y;
+    }
+    if (fv > H) {  // the last state
+      bool nr = false;
+      if (RECHECK) nr = fabsf(lim - fabsf(own)) < eps;
+      bool ok = (fabsf(own) < lim) | !boxed;
+      ok &= sr.track(group_lane<8, 0>(own), group_lane<8, 1>(own), &nr);
+      near |= nr;
+      const unsigned long long okm = __ballot(ok);
+      if (((okm >> base) & 0xFFull) != 0xFFull) fv = H;
+    }
+    if (fv_out && h == 0) fv_out[c] = (int16_t)fv;
+  }
+  // Some lane of the group saw a near margin.
+  const unsigned long long nm = __ballot(near);
+  near = ((nm >> base) & 0xFFull) != 0;
+  split_finish<MS, RECHECK>(md, gp, H, u_user, cand, slot, out, rl, lead, near, c, fv, cst);
+}
+
+// What every instance takes, in one place.
+struct SplitLaunch {
+  unsigned grid;
+  int block, split;
+  hipStream_t st;
+  const ModelDev* md;
+  GenParams gp;
+  int H;
+  const float *x_t, *u_user, *cand;
+  Slot* slot;
+  mpmi_selection* out;
+  int16_t* fv;
+  RecheckList* rl;
+  const mpmi_selection* gate;
+};
+
+template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED>
+static void split_launch(const SplitLaunch& a) {
+  tick_split_kernel<BASIS, SPLIT, DEG, TRACK, RECHECK, GATED><<<a.grid, a.block, 0, a.st>>>(
+      a.md, a.gp, a.H, a.x_t, a.u_user, a.cand, a.slot, a.out, a.fv, a.rl, a.gate);
+}
+template <int BASIS, int DEG, bool TRACK, bool RECHECK, bool GATED>
+static void split_lanes(const SplitLaunch& a) {
+  if (a.split == 2) split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED>(a);
+  else if (a.split == 4) split_launch<BASIS, 4, DEG, TRACK, RECHECK, GATED>(a);
+  else split_launch<BASIS, 8, DEG, TRACK, RECHECK, GATED>(a);
+}
+template <bool RECHECK, bool GATED>
+static void split_race_car(const mpmi_system& sys, const SplitLaunch& a) {
+  if (!sys.has_track) split_lanes<MPMI_BASIS_RACE_CAR, 1, false, RECHECK, GATED>(a);
+  else if (track_degree(sys) <= kSmallTrackDeg)
+    split_lanes<MPMI_BASIS_RACE_CAR, kSmallTrackDeg, true, RECHECK, GATED>(a);
+  else split_lanes<MPMI_BASIS_RACE_CAR, kMaxHarm, true, RECHECK, GATED>(a);
+}
+template <bool TRACK, bool RECHECK>
+static void split_custom(const SplitLaunch& a) {
+  tick_custom_split_kernel<TRACK, RECHECK><<<a.grid, a.block, 0, a.st>>>(a.md, a.gp, a.H, a.x_t, a.u_user, a.cand,
+                                                                        a.slot, a.out, a.fv, a.rl);
+}
+template <bool RECHECK>
+static void split_basis(const mpmi_system& sys, const SplitLaunch& a) {
+  if (sys.basis == MPMI_BASIS_CUSTOM) {
+    if (sys.has_track) split_custom<true, RECHECK>(a);
+    else split_custom<false, RECHECK>(a);
+  } else if (sys.basis == MPMI_BASIS_RACE_CAR) {
+    if (a.gate) split_race_car<RECHECK, true>(sys, a);
+    else split_race_car<RECHECK, false>(sys, a);
+  } else {
+    if (sys.has_track) split_lanes<MPMI_BASIS_BALANCE_BOT, kMaxHarm, true, RECHECK, false>(a);
+    else split_lanes<MPMI_BASIS_BALANCE_BOT, 1, false, RECHECK, false>(a);
+  }
 }
 
 hipError_t launch_tick_split(const mpmi_system& sys, int split, const void* model, const mpmi_tick_desc& d,
                              const float* x_t, const float* u_user, const float* cand, void* slot,
-                             mpmi_selection* out, int16_t* fv, hipStream_t st) {
-  GenParams gp;
-  gp.seed = d.seed;
-  gp.tick = d.tick;
-  gp.loop = d.loop;
-  gp.gen = d.gen;
-  gp.n_cand = d.n_cand;
-  gp.n_seg = d.n_seg;
-  for (int j = 0; j < MPMI_MAX_INPUT; ++j) gp.grid[j] = d.grid[j] > 0 ? d.grid[j] : 1;
-  const int block = d.block > 0 ? d.block : 256;
-  const unsigned grid = (unsigned)((((long long)d.n_cand + 1) * split + block - 1) / block);
-  const ModelDev* md = (const ModelDev*)model;
-  Slot* sl = (Slot*)slot;
-  const int H = d.horizon;
-  const bool small = track_degree(sys) <= kSmallTrackDeg;
-  if (sys.basis == MPMI_BASIS_RACE_CAR) {
-    if (!sys.has_track)
-      split_dispatch<MPMI_BASIS_RACE_CAR, 1, false>(split, grid, block, st, md, gp, H, x_t, u_user, cand, sl, out, fv);
-    else if (small)
-      split_dispatch<MPMI_BASIS_RACE_CAR, kSmallTrackDeg, true>(split, grid, block, st, md, gp, H, x_t, u_user, cand,
-                                                                sl, out, fv);
-    else
-      split_dispatch<MPMI_BASIS_RACE_CAR, kMaxHarm, true>(split, grid, block, st, md, gp, H, x_t, u_user, cand, sl,
-                                                          out, fv);
-  } else {
-    if (!sys.has_track)
-      split_dispatch<MPMI_BASIS_BALANCE_BOT, 1, false>(split, grid, block, st, md, gp, H, x_t, u_user, cand, sl, out,
-                                                       fv);
-    else
-      split_dispatch<MPMI_BASIS_BALANCE_BOT, kMaxHarm, true>(split, grid, block, st, md, gp, H, x_t, u_user, cand, sl,
-                                                             out, fv);
-  }
-  return hipGetLastError();
+                             mpmi_selection* out, int16_t* fv, hipStream_t st, const mpmi_selection* gate,
+                             void* recheck, int recheck_capacity, int recheck_grid) {
+  if (gate && sys.basis != MPMI_BASIS_RACE_CAR) return hipErrorInvalidValue;  // only race-car ticks are gated
+  SplitLaunch a;
+  a.gp.seed = d.seed;
+  a.gp.tick = d.tick;
+  a.gp.loop = d.loop;
+  a.gp.gen = d.gen;
+  a.gp.n_cand = d.n_cand;
+  a.gp.n_seg = d.n_seg;
+  for (int j = 0; j < MPMI_MAX_INPUT; ++j) a.gp.grid[j] = d.grid[j] > 0 ? d.grid[j] : 1;
+  a.block = d.block > 0 ? d.block : 256;
+  a.split = split;
+  a.grid = (unsigned)((((long long)d.n_cand + 1) * split + a.block - 1) / a.block);
+  a.st = st;
+  a.md = (const ModelDev*)model;
+  a.H = d.horizon;
+  a.x_t = x_t;
+  a.u_user = u_user;
+  a.cand = cand;
+  a.slot = (Slot*)slot;
+  a.out = out;
+  a.fv = fv;
+  a.rl = (RecheckList*)recheck;
+  a.gate = gate;
+  if (recheck) split_basis<true>(sys, a);
+  else split_basis<false>(sys, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !recheck) return e;
+  return launch_recheck64(sys, model, d, x_t, u_user, cand, slot, out, fv, recheck, recheck_capacity, recheck_grid,
+                          st, gate);
 }
 
 }  // namespace mpmi
