@@ -542,31 +542,31 @@ __device__ __forceinline__ double fma3s(double a, double b, double c) {
 // correctly rounded values; |x| >= 2^20 (and NaN, +-inf) take the library's
 // sincos, whose reduction holds for any argument.
 // ---------------------------------------------------------------------------
+constexpr double kTwoOverPi = 0x1.45f306dc9c883p-1;
+constexpr double kHalfPi1 = 0x1.921fb54442d18p+0;
+constexpr double kHalfPi2 = 0x1.1a62633145c07p-54;
+// (-1)^n / (2n + 1)!, n = 8 .. 1, and (-1)^n / (2n)!, n = 8 .. 2
+constexpr int kSinTerms = 8, kCosTerms = 7;
+constexpr double kSinSeries[kSinTerms] = {1.0 / 355687428096000.0, -1.0 / 1307674368000.0, 1.0 / 6227020800.0,
+                                          -1.0 / 39916800.0,       1.0 / 362880.0,         -1.0 / 5040.0,
+                                          1.0 / 120.0,             -1.0 / 6.0};
+constexpr double kCosSeries[kCosTerms] = {1.0 / 20922789888000.0, -1.0 / 87178291200.0, 1.0 / 479001600.0,
+                                          -1.0 / 3628800.0,       1.0 / 40320.0,        -1.0 / 720.0,
+                                          1.0 / 24.0};
 __device__ __forceinline__ void sincos_rr64(double x, double* sn, double* cs) {
   if (!(fabs(x) < 0x1p20)) {
     sincos(x, sn, cs);
     return;
   }
-  constexpr double kTwoOverPi = 0x1.45f306dc9c883p-1;
-  constexpr double kP1 = 0x1.921fb54442d18p+0;
-  constexpr double kP2 = 0x1.1a62633145c07p-54;
   const double k = rint(x * kTwoOverPi);
-  const double r = fma(-k, kP2, fma(-k, kP1, x));
+  const double r = fma(-k, kHalfPi2, fma(-k, kHalfPi1, x));
   const double z = r * r;
-  // (-1)^n / (2n + 1)!, n = 8 .. 1, and (-1)^n / (2n)!, n = 8 .. 2
-  double ps = fma3(1.0 / 355687428096000.0, z, -1.0 / 1307674368000.0);
-  ps = fma3(ps, z, 1.0 / 6227020800.0);
-  ps = fma3(ps, z, -1.0 / 39916800.0);
-  ps = fma3(ps, z, 1.0 / 362880.0);
-  ps = fma3(ps, z, -1.0 / 5040.0);
-  ps = fma3(ps, z, 1.0 / 120.0);
-  ps = fma3(ps, z, -1.0 / 6.0);
-  double pc = fma3(1.0 / 20922789888000.0, z, -1.0 / 87178291200.0);
-  pc = fma3(pc, z, 1.0 / 479001600.0);
-  pc = fma3(pc, z, -1.0 / 3628800.0);
-  pc = fma3(pc, z, 1.0 / 40320.0);
-  pc = fma3(pc, z, -1.0 / 720.0);
-  pc = fma3(pc, z, 1.0 / 24.0);
+  double ps = fma3(kSinSeries[0], z, kSinSeries[1]);
+#pragma unroll
+  for (int n = 2; n < kSinTerms; ++n) ps = fma3(ps, z, kSinSeries[n]);
+  double pc = fma3(kCosSeries[0], z, kCosSeries[1]);
+#pragma unroll
+  for (int n = 2; n < kCosTerms; ++n) pc = fma3(pc, z, kCosSeries[n]);
   const double s = fma(r * z, ps, r);                   // r + r z (-1/6 + ...)
   const double c = fma(z * z, pc, fma(-0.5, z, 1.0));   // 1 - z/2 + z^2 (1/24 + ...)
   const int q = (int)k;  // |k| < 2^20

@@ -19,9 +19,8 @@
 //
 // The launch is latency-bound: a tick keeps from none to a few thousand
 // candidates, each a serial H-step FP64 prediction.  The race car spreads one
-// candidate over eight lanes (one output component each, the step's
-// coefficients read from LDS) and holds eight per 64-lane workgroup; the
-// described bases run one candidate per lane, the atoms going through a
+// candidate over sixteen lanes (one output component each, the step's
+// coefficients in registers), or eight when many are kept; the described bases run one candidate per lane, the atoms going through a
 // per-lane column of LDS.  The many-loop form lists (loop, candidate, model)
 // entries and prunes by each loop's K* itself.
 #include <hip/hip_runtime.h>
@@ -391,6 +390,222 @@ __device__ int evaluate64_rc8(const ModelDev* __restrict__ md, const double* __r
   return H + 1;
 }
 
+// Value of v in lane SRC of this lane's row of 16, by one DPP move (row_newbcast
+// takes a whole double).
+template <int SRC>
+__device__ __forceinline__ double row_lane(double v) {
+  return __builtin_amdgcn_mov_dpp(v, 0x150 + SRC, 0xF, 0xF, true);
+}
+
+// fma and product that keep their place in the source's order among themselves.
+__device__ __forceinline__ double fma_here(double a, double b, double c) {
+  double d;
+  asm volatile("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+__device__ __forceinline__ double mul_here(double a, double b) {
+  double d;
+  asm volatile("v_mul_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+
+// rc_column64's inner sums, one term after the other over the eight chains
+// (t_0 .. t_5, ts, tc), each chain in its own order: the chain of a term, its
+// row of the step table and its component of the state.
+constexpr int kColumnTerms = kRcStepRows;
+constexpr signed char kColumnTerm[kColumnTerms][3] = {
+    {0, 0, 0},  {1, 6, 1},  {2, 11, 2}, {3, 15, 3}, {4, 18, 4}, {5, 20, 5}, {6, 21, 3}, {7, 24, 3}, {0, 1, 1},
+    {1, 7, 2},  {2, 12, 3}, {3, 16, 4}, {4, 19, 5}, {6, 22, 4}, {7, 25, 4}, {0, 2, 2},  {1, 8, 3},  {2, 13, 4},
+    {3, 17, 5}, {6, 23, 5}, {7, 26, 5}, {0, 3, 3},  {1, 9, 4},  {2, 14, 5}, {0, 4, 4},  {1, 10, 5}, {0, 5, 5}};
+
+// What a lane of evaluate64_rc16 holds through the horizon.
+template <int DEG>
+struct RcLane64 {
+  static constexpr int kHorner = DEG + 1 > kSinTerms ? DEG + 1 : kSinTerms;
+  double kc[kRcStepRows];  // column j of the step rows
+  double hc[kHorner];      // this lane's polynomial, leading coefficient first
+  double lim, trk_lim;     // component j's box, the track's half width
+  bool box, track;
+};
+template <int DEG>
+__device__ __forceinline__ RcLane64<DEG> rc_lane64(const Model64* __restrict__ m, int j, int role) {
+  RcLane64<DEG> ln;
+  constexpr int NH = RcLane64<DEG>::kHorner;
+#pragma unroll
+  for (int r = 0; r < kRcStepRows; ++r) ln.kc[r] = m->Kstep[r][j];
+#pragma unroll
+  for (int n = 0; n < NH; ++n) {
+    const int q = NH - 1 - n;  // the power
+    const double s = q < kSinTerms ? kSinSeries[q < kSinTerms ? kSinTerms - 1 - q : 0] : 0.0;
+    const double c = q < kCosTerms ? kCosSeries[q < kCosTerms ? kCosTerms - 1 - q : 0] : 0.0;
+    const double P = q <= DEG ? m->trk_p[q <= DEG ? q : 0] : 0.0;
+    const double Q = q < DEG ? m->trk_q[q < DEG ? q : 0] : 0.0;
+    ln.hc[n] = role == 0 ? s : (role == 1 ? c : (role == 2 ? P : Q));
+  }
+  ln.lim = m->comp_lim[j];
+  ln.trk_lim = m->trk_lim;
+  ln.box = (m->comp_mask >> j) & 1;
+  ln.track = m->has_track != 0;
+  return ln;
+}
+
+// Race car, one candidate over a row of 16 lanes.  Lane j (< 6) holds output
+// column j's coefficients in registers and forms x'_j (lanes 6 and up repeat
+// column 5); one DPP move per component gives every lane the new state (the
+// same bits, so the same verdict and the same exit step).  The step's four
+// polynomials, the heading's sine and cosine series and the centreline's P and
+// Q, run as one Horner chain: lane l evaluates number l % 4 at its own
+// argument, and DPP moves hand the four values round.  Leading zero
+// coefficients leave a partial sum unchanged.  The noise draws are formed by
+// every lane; lane j tests component j's box.  Returns the first violation
+// (1..H, or H + 1).  FAR: the library's sine and cosine, for any heading; the
+// other form returns -1 when a heading leaves the reduction's range (its caller
+// then takes FAR), so that the library code's registers do not weigh on the
+// loop.
+//
+// Bound: one wave's chain, about 770 cycles per step against about 1400 for
+// the 8-lane form (its coefficients come from LDS at every step, and its
+// exchange goes through it): a 60-step tick of 16,384 candidates that keeps a
+// few hundred takes 70 us, 85 us by the 8-lane form (43 us with none kept).
+// Of its step neither the column's terms, the exit nor 1 / rho shows when it is
+// taken out; the heading's series and its exchange do.
+template <int DEG, bool NOISE, bool FAR>
+__device__ __forceinline__ int evaluate64_rc16(const ModelDev* __restrict__ md, RcLane64<DEG>& ln,
+                                               const GenParams& gp, int H, const float* __restrict__ x_t,
+                                               const float* __restrict__ u_user, const float* __restrict__ cand,
+                                               int c, bool valid, int j, int role) {
+  const Model64* m = &md->m64;
+  const int row = threadIdx.x & 48;
+  // Horizon and segments are the same for the wave's four rows, so the loop is
+  // uniform: a row that has ended idles along (its values are not used) until
+  // the last one has.
+  unsigned long long live = __builtin_amdgcn_ballot_w64(valid);
+  int fv = H + 1;
+  const int S = gp.n_seg;
+  double x[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) x[k] = (double)x_t[k];
+  const uint64_t pre = NOISE ? hash_prefix(gp.seed, gp.tick, (uint64_t)(uint32_t)gp.loop, (uint64_t)c) : 0ull;
+  const bool on_track = role >= 2, is_sin = role == 0;
+  // Iteration s forms x_s from x_{s-1} and, beside it, the verdict of
+  // x_{s-1} (the two are independent, so their chains overlap); an unsafe
+  // x_{s-1} ends the rollout at s - 1 and the step formed with it is dropped.
+  double own = 0.0;  // component j of the state being checked
+  int s = 1;
+  for (int g = 0; g < S; ++g) {
+    const int last = min(H, segment_start(g + 1, S, H) - 1);  // the segment's last step
+    if (s > last) continue;                                   // more segments than steps
+    double cu, L[6], Ts, Tc;
+    {
+      const double d = (double)cand_value(gp, md, cand, u_user, c, g, 0);
+      const double a = (double)cand_value(gp, md, cand, u_user, c, g, 1);
+      double sd, cd;
+      sincos(d, &sd, &cd);
+      fold_column64(opaque_coeffs(&m->K[0][0]), j, d, a, sd, cd, &cu, L, &Ts, &Tc);
+    }
+    // Held in registers: the compiler would read them again at every step.
+#pragma unroll
+    for (int r = 0; r < kRcStepRows; ++r) asm volatile("" : "+v"(ln.kc[r]));
+#pragma unroll
+    for (int n = 0; n < RcLane64<DEG>::kHorner; ++n) asm volatile("" : "+v"(ln.hc[n]));
+    asm volatile("" : "+v"(ln.lim), "+v"(ln.trk_lim));
+    for (; s <= last; ++s) {
+      // x_{s-1}'s polynomials, with the column's terms in the gaps of their
+      // chains (dependent, an operation takes the time of two).  1 / rho as in
+      // track_ok64, the heading's reduction as in sincos_rr64.
+      double tc[8] = {L[0], L[1], L[2], L[3], L[4], L[5], Ts, Tc};
+      constexpr int NH = RcLane64<DEG>::kHorner;
+      constexpr int kFirst = kColumnTerms - 2 * (NH - 2);  // terms before the Horner chain
+      static_assert(kFirst >= 11, "terms for the gaps of the 1 / rho chain");
+      auto terms = [&](int from, int to) {
+#pragma unroll
+        for (int i = from; i < to; ++i) {
+          const int q = kColumnTerm[i][0];
+          tc[q] = fma_here(ln.kc[kColumnTerm[i][1]], x[kColumnTerm[i][2]], tc[q]);
+        }
+      };
+      const double kq = rint(x[2] * kTwoOverPi);
+      const double yy = mul_here(x[1], x[1]);
+      terms(0, 1);
+      const double r2 = fma_here(x[0], x[0], yy);
+      terms(1, 2);
+      double inv = __builtin_amdgcn_rsq(r2);
+      const double hr = -0.5 * r2;
+      double ii = inv * inv;
+      terms(2, 4);
+      ii = fma_here(hr, ii, 1.5);
+      terms(4, 5);
+      inv = mul_here(inv, ii);
+      const double t = fma(-kq, kHalfPi2, fma(-kq, kHalfPi1, x[2]));
+      terms(5, 6);
+      ii = mul_here(inv, inv);
+      terms(6, 7);
+      ii = fma_here(hr, ii, 1.5);
+      const double z = t * t;
+      terms(7, 8);
+      inv = mul_here(inv, ii);
+      terms(8, 10);
+      const double c1 = mul_here(x[0], inv);
+      terms(10, kFirst);
+      const double rho = r2 * inv, s1 = x[1] * inv;
+      const double arg = on_track ? c1 : z;
+      double h = ln.hc[0];
+#pragma unroll
+      for (int n = 1; n < NH - 1; ++n) {
+        h = fma_here(h, arg, ln.hc[n]);
+        terms(kFirst + 2 * (n - 1), kFirst + 2 * n);
+      }
+      h = fma(h, arg, ln.hc[NH - 1]);
+      const double ya = fma_here(x[1], tc[1], fma_here(x[3], tc[3], mul_here(x[5], tc[5])));
+      const double yb = fma_here(x[0], tc[0], fma_here(x[2], tc[2], mul_here(x[4], tc[4])));
+      double sp, cp;
+      if constexpr (FAR) {
+        sincos_rr64(x[2], &sp, &cp);
+      } else {
+        const double v = fma(z * (is_sin ? t : z), h, is_sin ? t : fma(-0.5, z, 1.0));
+        const double s0 = row_lane<0>(v), c0 = row_lane<1>(v);
+        const int q = (int)kq;  // |kq| < 2^20 where the result is used
+        const bool swap = (q & 1) != 0;
+        const double sv = swap ? c0 : s0, cv = swap ? s0 : c0;
+        sp = (q & 2) ? -sv : sv;
+        cp = ((q + 1) & 2) ? -cv : cv;
+      }
+      double y = (fma(cp, tc[7], fma(sp, tc[6], cu)) + ya) + yb;  // rc_column64
+      // Formed above the exit, where it fills the polynomials' chain.
+      asm volatile("" : "+v"(y));
+      // safe64's verdict, lane j on component j's box; x_0, the current state,
+      // is not checked.  One ballot decides the usual case, that every row goes on.
+      const double P = row_lane<2>(h), Q = row_lane<3>(h);
+      const bool ok = (fabs(own) < ln.lim || !ln.box) && (fabs(rho - fma(s1, Q, P)) < ln.trk_lim || !ln.track);
+      const bool near = FAR || fabs(x[2]) < 0x1p20;
+      if ((__builtin_amdgcn_ballot_w64(!(ok && near)) & live) != 0ull) {
+        const bool bad = s > 1 && ((__builtin_amdgcn_ballot_w64(!ok) >> row) & 0xFFFFull) != 0ull;
+        const bool ends = ((live >> row) & 1ull) != 0ull && (bad || !near);
+        if (ends) fv = bad ? s - 1 : -1;
+        live &= ~__builtin_amdgcn_ballot_w64(ends);
+        if (live == 0ull) return fv;
+      }
+      x[0] = row_lane<0>(y);
+      x[1] = row_lane<1>(y);
+      x[2] = row_lane<2>(y);
+      x[3] = row_lane<3>(y);
+      x[4] = row_lane<4>(y);
+      x[5] = row_lane<5>(y);
+      own = y;
+      if constexpr (NOISE) {
+        add_noise64(m, pre, s, 6, x);
+        own = x[0];
+#pragma unroll
+        for (int k = 1; k < 6; ++k) own = (j == k) ? x[k] : own;
+      }
+    }
+  }
+  const bool box_ok = fabs(own) < ln.lim || !ln.box;
+  const bool boxes_ok = ((__builtin_amdgcn_ballot_w64(!box_ok) >> row) & 0xFFFFull) == 0ull;
+  if (((live >> row) & 1ull) != 0ull && !(boxes_ok && track_ok64(safety64<6, DEG>(m), x))) fv = H;
+  return fv;
+}
+
 // ---------------------------------------------------------------------------
 // Single loop: re-roll the context's list, publish, finalise.
 // ---------------------------------------------------------------------------
@@ -514,16 +729,19 @@ recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const flo
   recheck_publish(md, gp, H, u_user, cand, slot, out, rl, ks, kf, n_safe, (unsigned int)parts);
 }
 
-// Race car: one kept candidate per 8-lane group (evaluate64_rc8), eight per
-// workgroup.
-template <int DEG>
+// Race car: four kept candidates to a wave (evaluate64_rc16), or eight
+// (evaluate64_rc8) where four would take more than two waves per SIMD.  One
+// wave per workgroup.  The 16-lane form's chain is the shorter, the 8-lane form
+// does less per candidate.  1,048,576 candidates, 60 steps: with 6,986 kept 462
+// us by 16 lanes and 466 by 8; with 12,117 kept 500 us by 16 lanes and 473 by 8.
+constexpr int kRowEntries = 8192;
+template <int DEG, bool NOISE>
 __global__ void __launch_bounds__(kR64Block, 2)
 recheck64_rc_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
                     const float* __restrict__ u_user, const float* __restrict__ cand, Slot* __restrict__ slot,
                     mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out, RecheckList* __restrict__ rl,
                     int capacity, const mpmi_selection* __restrict__ gate) {
   static_assert(kR64Block == 64, "one wave per workgroup");
-  constexpr int kPer = kR64Block / 8;  // candidates per workgroup pass
   __shared__ double sK[MPMI_MAX_DIM * 8];
   __shared__ double sKs[kRcStepRows * 8];
   // Gated tick (a fallback after a proposal tick): nothing ran, nothing to finalise.
@@ -531,28 +749,48 @@ recheck64_rc_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const 
   const unsigned int kn = rl->n_keep;
   const int n_keep = (int)(kn < (unsigned int)capacity ? kn : (unsigned int)capacity);
   if (recheck_nothing_kept(md, gp, H, u_user, cand, slot, out, rl, n_keep)) return;
-  const int parts = min((int)gridDim.x, (n_keep + kPer - 1) / kPer);
+  const bool rows = n_keep <= kRowEntries;
+  const int per = rows ? kR64Block / 16 : kR64Block / 8;  // candidates per workgroup pass
+  const int parts = min((int)gridDim.x, (n_keep + per - 1) / per);
   if ((int)blockIdx.x >= parts) return;  // uniform
   const int* keep = rl->idx + capacity;
   const int lane = threadIdx.x;
   unsigned long long ks = kKeyNone, kf = kKeyNone;
   unsigned int n_safe = 0;
-  const double* Kg = &md->m64.K[0][0];
-  for (int e = lane; e < MPMI_MAX_DIM * 8; e += kR64Block) sK[e] = Kg[e];
-  for (int e = lane; e < kRcStepRows * 8; e += kR64Block) sKs[e] = (&md->m64.Kstep[0][0])[e];
-  __syncthreads();
-  for (int q = blockIdx.x * kPer + (lane >> 3); q < n_keep; q += parts * kPer) {  // uniform per 8-lane group
-    const int c = keep[q] >> 1;
-    const int fv = evaluate64_rc8<DEG>(md, sK, sKs, gp, H, x_t, u_user, cand, c);
-    if ((lane & 7) == 0) {
-      if (fv_out) fv_out[c] = (int16_t)fv;
-      const float cst = cost_at(md, gp, cand, u_user, c);
-      const bool safe = fv == H + 1;
-      const unsigned long long a = safe ? safe_key(cst, c) : kKeyNone;
-      const unsigned long long b = safe ? kKeyNone : fallback_key(fv, cst, c);
-      ks = a < ks ? a : ks;
-      kf = b < kf ? b : kf;
-      n_safe += (safe && c > 0) ? 1u : 0u;
+  auto publish = [&](int c, int fv) {  // one lane per candidate
+    if (fv_out) fv_out[c] = (int16_t)fv;
+    const float cst = cost_at(md, gp, cand, u_user, c);
+    const bool safe = fv == H + 1;
+    const unsigned long long a = safe ? safe_key(cst, c) : kKeyNone;
+    const unsigned long long b = safe ? kKeyNone : fallback_key(fv, cst, c);
+    ks = a < ks ? a : ks;
+    kf = b < kf ? b : kf;
+    n_safe += (safe && c > 0) ? 1u : 0u;
+  };
+  if (rows) {
+    const int j = min(lane & 15, 5), role = lane & 3;
+    RcLane64<DEG> ln = rc_lane64<DEG>(&md->m64, j, role);
+    for (int q0 = blockIdx.x * per; q0 < n_keep; q0 += parts * per) {  // uniform
+      const int q = q0 + (lane >> 4);
+      const bool valid = q < n_keep;
+      const int c = keep[valid ? q : n_keep - 1] >> 1;
+      int fv = evaluate64_rc16<DEG, NOISE, false>(md, ln, gp, H, x_t, u_user, cand, c, valid, j, role);
+      if (__builtin_amdgcn_ballot_w64(valid && fv < 0) != 0ull) {
+        const int far = evaluate64_rc16<DEG, NOISE, true>(md, ln, gp, H, x_t, u_user, cand, c, valid && fv < 0, j,
+                                                          role);
+        fv = fv < 0 ? far : fv;
+      }
+      if (valid && (lane & 15) == 0) publish(c, fv);
+    }
+  } else {
+    const double* Kg = &md->m64.K[0][0];
+    for (int e = lane; e < MPMI_MAX_DIM * 8; e += kR64Block) sK[e] = Kg[e];
+    for (int e = lane; e < kRcStepRows * 8; e += kR64Block) sKs[e] = (&md->m64.Kstep[0][0])[e];
+    __syncthreads();
+    for (int q = blockIdx.x * per + (lane >> 3); q < n_keep; q += parts * per) {  // uniform per 8-lane group
+      const int c = keep[q] >> 1;
+      const int fv = evaluate64_rc8<DEG>(md, sK, sKs, gp, H, x_t, u_user, cand, c);
+      if ((lane & 7) == 0) publish(c, fv);
     }
   }
   recheck_publish(md, gp, H, u_user, cand, slot, out, rl, ks, kf, n_safe, (unsigned int)parts);
@@ -575,14 +813,12 @@ hipError_t launch_recheck64(const mpmi_system& sys, const void* model, const mpm
   const bool small = track_degree(sys) <= kSmallTrackDeg;
   recheck64_filter_kernel<<<grid, kFilterBlock, 0, st>>>(md, gp, u_user, cand, sl, rl, capacity);
   if (sys.basis == MPMI_BASIS_RACE_CAR) {
-    // Windows of 8 entries, one wave per workgroup, up to three waves per
-    // SIMD: 16 workgroups per compute unit cover 32,768 entries per pass.
-    if (small)
-      recheck64_rc_kernel<kSmallTrackDeg><<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl,
-                                                                          out, fv, rl, capacity, gate);
-    else
-      recheck64_rc_kernel<kMaxHarm><<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out,
-                                                                    fv, rl, capacity, gate);
+    // One wave per workgroup, two per SIMD: 16 workgroups per compute unit
+    // leave the second half of a longer list to start as waves end.
+    const bool noisy = system_noisy(sys);
+    auto kern = small ? (noisy ? recheck64_rc_kernel<kSmallTrackDeg, true> : recheck64_rc_kernel<kSmallTrackDeg, false>)
+                      : (noisy ? recheck64_rc_kernel<kMaxHarm, true> : recheck64_rc_kernel<kMaxHarm, false>);
+    kern<<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl, capacity, gate);
   } else if (small) {
     recheck64_kernel<kSmallTrackDeg><<<grid, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv,
                                                                  rl, capacity, gate);
