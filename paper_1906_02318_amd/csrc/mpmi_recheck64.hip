@@ -20,8 +20,9 @@
 // The launch is latency-bound: a tick keeps from none to a few thousand
 // candidates, each a serial H-step FP64 prediction.  The race car spreads one
 // candidate over sixteen lanes (one output component each, the step's
-// coefficients in registers), or eight when many are kept; the described bases run one candidate per lane, the atoms going through a
-// per-lane column of LDS.  The many-loop form lists (loop, candidate, model)
+// coefficients in registers), or eight when many are kept; the described bases
+// spread one over sixteen (an atom or two, four features and an output
+// component each), or run one per lane when very many are kept.  The many-loop form lists (loop, candidate, model)
 // entries and prunes by each loop's K* itself.
 #include <hip/hip_runtime.h>
 
@@ -691,8 +692,152 @@ __device__ __forceinline__ bool recheck_nothing_kept(const ModelDev* __restrict_
   return true;
 }
 
-// Described bases: one kept candidate per lane.
-template <int DEG>
+// y0, y1 += the products p of the row's lanes 0 .. 15, in order, times k, even
+// lanes to y0 and odd lanes to y1: one instruction each (row_newbcast).  The
+// wait is the two states a DPP read needs after the write of p.
+__device__ __forceinline__ void add_sixteen64(double p, const double* k, double& y0, double& y1) {
+  asm("s_nop 1\n"
+      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:0 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %4 row_newbcast:1 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %2, %5 row_newbcast:2 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %6 row_newbcast:3 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %2, %7 row_newbcast:4 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %8 row_newbcast:5 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %2, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %10 row_newbcast:7 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %2, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %12 row_newbcast:9 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %2, %13 row_newbcast:10 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %14 row_newbcast:11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %2, %15 row_newbcast:12 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %16 row_newbcast:13 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %2, %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %2, %18 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+      : "+v"(y0), "+v"(y1)
+      : "v"(p), "v"(k[0]), "v"(k[1]), "v"(k[2]), "v"(k[3]), "v"(k[4]), "v"(k[5]), "v"(k[6]), "v"(k[7]), "v"(k[8]),
+        "v"(k[9]), "v"(k[10]), "v"(k[11]), "v"(k[12]), "v"(k[13]), "v"(k[14]), "v"(k[15]));
+}
+
+// LDS of a row: w = [x; u] and the atoms, with a zero entry past the last.
+constexpr int kRowW = MPMI_MAX_STATE + MPMI_MAX_INPUT;
+constexpr int kRowLds = kRowW + MPMI_MAX_ATOMS + 1;
+
+// A basis given by its description, one candidate over a row of 16 lanes: lane
+// l evaluates atoms l and l + 16 and forms features l, l + 16, ..; lane j and
+// lane j + 8 sum output component j over all features (KD, a multiple of 16, at
+// least the basis size), test its box and hold its noise draw.  Returns the
+// first violation (1..H, or H + 1).
+//
+// Bound: one wave's chain per step, through LDS twice (atoms, products), a sine
+// and a cosine per lane, and one instruction per feature.  One candidate per
+// lane pays the sine and cosine of every atom one after the other, and every
+// feature for every component.  A balance-bot tick of 10,000 candidates, 50
+// steps, that keeps many of them: 183 to 46 us (24 us with none kept).
+template <int DEG, int KD, bool NOISE>
+__device__ __forceinline__ int evaluate64_row(const ModelDev* __restrict__ md, const GenParams& gp, int H,
+                                              const float* __restrict__ x_t, const float* __restrict__ u_user,
+                                              const float* __restrict__ cand, int c, bool valid, double* w) {
+  const Model64* m = &md->m64;
+  const int lane = threadIdx.x, r = lane & 15, j = r & 7, row = lane & 48;
+  const int n = md->n, mi = md->m, D = md->dim, na = m->n_atoms, S = gp.n_seg;
+  double* at = w + kRowW;
+  double k[KD];
+#pragma unroll
+  for (int f = 0; f < KD; ++f) k[f] = f < D ? m->K[f][j] : 0.0;
+  int fa[KD / 16], fb[KD / 16], kind[2], var[2];
+#pragma unroll
+  for (int i = 0; i < KD / 16; ++i) {
+    const int f = 16 * i + r;
+    fa[i] = f < D ? m->feat_a[f] : MPMI_MAX_ATOMS;
+    fb[i] = f < D ? m->feat_b[f] : MPMI_MAX_ATOMS;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int q = r + 16 * i;
+    kind[i] = q < na ? m->atom_kind[q] : MPMI_ATOM_ONE;
+    const int v = q < na ? m->atom_var[q] : 0;
+    var[i] = v < n ? v : MPMI_MAX_STATE + (v - n);
+  }
+  const double lim = m->comp_lim[j], sigma = m->sigma[j];
+  const bool box = (m->comp_mask >> j) & 1;
+  const Safety64<6, DEG> sc = safety64<6, DEG>(m);
+  const uint64_t pre = NOISE ? hash_prefix(gp.seed, gp.tick, (uint64_t)(uint32_t)gp.loop, (uint64_t)c) : 0ull;
+  if (r == 0) at[MPMI_MAX_ATOMS] = 0.0;
+  if (r < MPMI_MAX_STATE) w[r] = r < n ? (double)x_t[r] : 0.0;
+#pragma unroll
+  for (int f = 0; f < KD; ++f) asm volatile("" : "+v"(k[f]));
+  // As in evaluate64_rc16: the wave's rows go through the loop together, and
+  // step s carries the verdict of x_{s-1} beside it.
+  unsigned long long live = __builtin_amdgcn_ballot_w64(valid);
+  int fv = H + 1;
+  double own = 0.0;
+  auto verdict = [&]() {  // of the row's state; the row's lanes then agree
+    bool ok = fabs(own) < lim || !box;
+    if (m->has_track) {  // uniform
+      const double xy[2] = {row_lane<0>(own), row_lane<1>(own)};
+      ok = ok && track_ok64(sc, xy);
+    }
+    return ((__builtin_amdgcn_ballot_w64(!ok) >> row) & 0xFFFFull) == 0ull;
+  };
+  int s = 1;
+  for (int g = 0; g < S; ++g) {
+    const int last = min(H, segment_start(g + 1, S, H) - 1);  // the segment's last step
+    if (s > last) continue;                                   // more segments than steps
+    if (r < mi) w[MPMI_MAX_STATE + r] = (double)cand_value(gp, md, cand, u_user, c, g, r);
+    for (; s <= last; ++s) {
+      asm volatile("" ::: "memory");  // a wave's LDS accesses are in order
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (i == 0 || na > 16) {  // uniform
+          const double v = w[var[i]];
+          double sn, cs;
+          sincos_rr64(v, &sn, &cs);
+          double a = 1.0;
+          a = kind[i] == MPMI_ATOM_VAR ? v : a;
+          a = kind[i] == MPMI_ATOM_SIN ? sn : a;
+          a = kind[i] == MPMI_ATOM_COS ? cs : a;
+          at[r + 16 * i] = a;
+        }
+      }
+      asm volatile("" ::: "memory");
+      double p[KD / 16];
+#pragma unroll
+      for (int i = 0; i < KD / 16; ++i) p[i] = at[fa[i]] * at[fb[i]];
+      const bool ok = verdict();
+      double y0 = 0.0, y1 = 0.0;
+#pragma unroll
+      for (int i = 0; i < KD / 16; ++i)
+        if (i == 0 || D > 16 * i) add_sixteen64(p[i], k + 16 * i, y0, y1);  // uniform
+      double y = j < n ? y0 + y1 : 0.0;
+      if constexpr (NOISE) {  // add_noise64's draw of component j
+        const uint64_t h = hash_finish(pre, kNoiseSlot + 4ull * (uint64_t)(s - 1) + (uint64_t)(j >> 1));
+        const double u1 = ((double)(h >> 40) + 1.0) * 0x1p-24;
+        const double u2 = (double)((h >> 16) & 0xFFFFFFull) * 0x1p-24;
+        const double rad = sqrt(-2.0 * log(u1)), ang = 6.283185307179586 * u2;
+        y = y + (j < n ? sigma * (rad * ((j & 1) ? sin(ang) : cos(ang))) : 0.0);
+      }
+      if (s > 1 && (__builtin_amdgcn_ballot_w64(!ok) & live) != 0ull) {  // x_0 is not checked
+        if (!ok && ((live >> row) & 1ull) != 0ull) fv = s - 1;
+        live &= __builtin_amdgcn_ballot_w64(ok);
+        if (live == 0ull) return fv;
+      }
+      asm volatile("" ::: "memory");
+      if (r < MPMI_MAX_STATE) w[r] = y;
+      own = y;
+    }
+  }
+  const bool ok = verdict();
+  if (((live >> row) & 1ull) != 0ull && !ok) fv = H;
+  return fv;
+}
+
+// Described bases: one kept candidate per 16-lane row, or one per lane above
+// kRowEntriesDescribed, where the lane form's waves, full, do less in all.  A
+// tick with every candidate kept, rows and lanes: balance bot, 50 steps, 64
+// candidates 49 and 219 us, 8,192: 108 and 229, 32,768: 229 and 255, 49,152: 310
+// and 277; the three-input car, 64 features, 25 steps, 32,768: 299 and 391.
+constexpr int kRowEntriesDescribed = 32768;
+template <int DEG, int KD, bool NOISE>
 __global__ void __launch_bounds__(kR64Block)
 recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
                  const float* __restrict__ u_user, const float* __restrict__ cand, Slot* __restrict__ slot,
@@ -700,23 +845,21 @@ recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const flo
                  int capacity, const mpmi_selection* __restrict__ gate) {
   __shared__ double sK[MPMI_MAX_DIM * 8];
   __shared__ double sAt[MPMI_MAX_ATOMS * kR64Block];
+  static_assert(4 * kRowLds <= MPMI_MAX_ATOMS * kR64Block, "a wave's rows");
   // Gated tick (a fallback after a proposal tick): nothing ran, nothing to finalise.
   if (gate && gate->status == MPMI_OK) return;
   const unsigned int kn = rl->n_keep;
   const int n_keep = (int)(kn < (unsigned int)capacity ? kn : (unsigned int)capacity);
   if (recheck_nothing_kept(md, gp, H, u_user, cand, slot, out, rl, n_keep)) return;
-  const int parts = min((int)gridDim.x, (n_keep + kR64Block - 1) / kR64Block);
+  const bool rows = n_keep <= kRowEntriesDescribed;
+  const int per = rows ? kR64Block / 16 : kR64Block;  // candidates per workgroup pass
+  const int parts = min((int)gridDim.x, (n_keep + per - 1) / per);
   if ((int)blockIdx.x >= parts) return;  // uniform
   const int* keep = rl->idx + capacity;
   const int lane = threadIdx.x;
   unsigned long long ks = kKeyNone, kf = kKeyNone;
   unsigned int n_safe = 0;
-  const double* Kg = &md->m64.K[0][0];
-  for (int e = lane; e < MPMI_MAX_DIM * 8; e += kR64Block) sK[e] = Kg[e];
-  __syncthreads();
-  for (int e = blockIdx.x * kR64Block + lane; e < n_keep; e += parts * kR64Block) {
-    const int c = keep[e] >> 1;
-    const int fv = evaluate64<false, DEG>(md, sK, nullptr, gp, H, x_t, u_user, cand, c, sAt + lane);
+  auto publish = [&](int c, int fv) {  // one lane per candidate
     if (fv_out) fv_out[c] = (int16_t)fv;
     const float cst = cost_at(md, gp, cand, u_user, c);
     const bool safe = fv == H + 1;
@@ -725,8 +868,31 @@ recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const flo
     ks = a < ks ? a : ks;
     kf = b < kf ? b : kf;
     n_safe += (safe && c > 0) ? 1u : 0u;
+  };
+  if (rows) {
+    for (int q0 = blockIdx.x * per; q0 < n_keep; q0 += parts * per) {  // uniform
+      const int q = q0 + (lane >> 4);
+      const bool valid = q < n_keep;
+      const int c = keep[valid ? q : n_keep - 1] >> 1;
+      const int fv = evaluate64_row<DEG, KD, NOISE>(md, gp, H, x_t, u_user, cand, c, valid,
+                                                    sAt + (lane >> 4) * kRowLds);
+      if (valid && (lane & 15) == 0) publish(c, fv);
+    }
+  } else {
+    const double* Kg = &md->m64.K[0][0];
+    for (int e = lane; e < MPMI_MAX_DIM * 8; e += kR64Block) sK[e] = Kg[e];
+    __syncthreads();
+    for (int e = blockIdx.x * kR64Block + lane; e < n_keep; e += parts * kR64Block) {
+      const int c = keep[e] >> 1;
+      publish(c, evaluate64<false, DEG>(md, sK, nullptr, gp, H, x_t, u_user, cand, c, sAt + lane));
+    }
   }
   recheck_publish(md, gp, H, u_user, cand, slot, out, rl, ks, kf, n_safe, (unsigned int)parts);
+}
+
+template <int DEG, bool NOISE>
+static auto described_kernel(bool wide) {  // wide: more than 32 features
+  return wide ? recheck64_kernel<DEG, 64, NOISE> : recheck64_kernel<DEG, 32, NOISE>;
 }
 
 // Race car: four kept candidates to a wave (evaluate64_rc16), or eight
@@ -812,19 +978,18 @@ hipError_t launch_recheck64(const mpmi_system& sys, const void* model, const mpm
   RecheckList* rl = (RecheckList*)recheck;
   const bool small = track_degree(sys) <= kSmallTrackDeg;
   recheck64_filter_kernel<<<grid, kFilterBlock, 0, st>>>(md, gp, u_user, cand, sl, rl, capacity);
+  const bool noisy = system_noisy(sys);
+  // One wave per workgroup: 16 workgroups per compute unit leave the second half
+  // of a longer list to start as waves end.
   if (sys.basis == MPMI_BASIS_RACE_CAR) {
-    // One wave per workgroup, two per SIMD: 16 workgroups per compute unit
-    // leave the second half of a longer list to start as waves end.
-    const bool noisy = system_noisy(sys);
     auto kern = small ? (noisy ? recheck64_rc_kernel<kSmallTrackDeg, true> : recheck64_rc_kernel<kSmallTrackDeg, false>)
                       : (noisy ? recheck64_rc_kernel<kMaxHarm, true> : recheck64_rc_kernel<kMaxHarm, false>);
     kern<<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl, capacity, gate);
-  } else if (small) {
-    recheck64_kernel<kSmallTrackDeg><<<grid, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv,
-                                                                 rl, capacity, gate);
   } else {
-    recheck64_kernel<kMaxHarm><<<grid, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl,
-                                                           capacity, gate);
+    const bool wide = sys.basis == MPMI_BASIS_CUSTOM && sys.dim > 32;
+    auto kern = small ? (noisy ? described_kernel<kSmallTrackDeg, true>(wide) : described_kernel<kSmallTrackDeg, false>(wide))
+                      : (noisy ? described_kernel<kMaxHarm, true>(wide) : described_kernel<kMaxHarm, false>(wide));
+    kern<<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl, capacity, gate);
   }
   return hipGetLastError();
 }

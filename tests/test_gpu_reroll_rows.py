@@ -1,9 +1,10 @@
-"""The race car's FP64 re-roll over a whole list: bands so wide that every
-candidate is listed and nothing precedes the list, so every first violation
-is the re-roll's.  Against the many-loop form, which predicts one candidate
-per lane.  The two add the same terms in other orders, so a verdict could
-differ only where a margin is within some 1e-13 of zero; over the at most
-8,193 x 60 margins of a case, of spread about one, that is a chance of 1e-7."""
+"""The FP64 re-roll over a whole list: bands so wide that every candidate is
+listed and nothing precedes the list, so every first violation is the
+re-roll's.  The fixed bases against the many-loop form, which predicts one
+candidate per lane, the described ones against a float64 prediction here.  The
+two add the same terms in other orders, so a verdict could differ only where a
+margin is within some 1e-13 of zero; over the at most 32,769 x 60 margins of a
+case, of spread about one, that is a chance of 1e-6."""
 from __future__ import annotations
 
 import numpy as np
@@ -31,18 +32,35 @@ def _turning_model():
                                              (8191, 60, 2, None, False), (8192, 60, 2, None, False),
                                              (70, 40, 4, 2.0 ** 20 - 20, False), (8192, 40, 4, 2.0 ** 20 - 20, False),
                                              (9, 12, 1, 3e6, False)])
-def test_every_first_violation_is_the_one_lane_forms(N, H, S, psi, noise):
+def test_race_car_first_violations_are_the_one_lane_forms(N, H, S, psi, noise):
     ctx = mpmi.Context(0)
     sys = mpmi.race_car_system(W.track_dict(W.rc_track()), eps32_track=1e30, eps32_vy=1e30,
                                noise=[1e-3, 0.0, 1e-4, 0.0, 2e-3, 1e-3] if noise else None)
     K = W.rc_model()[0] if psi is None else _turning_model()
     model = mpmi.mpmi_model_pack(ctx, sys, torch.tensor(K, device="cuda"))
-    states, users = synth.race_car_states(3, W.rc_track(), seed=21), synth.uniform_user(
-        3, synth.RC_U_LO, synth.RC_U_HI, seed=22)
+    states = synth.race_car_states(3, W.rc_track(), seed=21)
+    if psi is not None:
+        states[:, 2] = psi
+    _against_the_many_loop_form(ctx, model, states, synth.uniform_user(3, synth.RC_U_LO, synth.RC_U_HI, seed=22), N, H, S)
+
+
+# both sides of the 16-lane form's limit, headings on both sides of the reduction's range, and process noise
+@pytest.mark.parametrize("N,H,S,theta,noise", [(0, 3, 1, None, False), (2, 50, 5, None, False), (4, 5, 8, None, False),
+                                               (260, 50, 7, None, True), (32767, 20, 2, None, False),
+                                               (32768, 20, 2, None, False), (70, 20, 4, 2.0 ** 20, False)])
+def test_balance_bot_first_violations_are_the_one_lane_forms(N, H, S, theta, noise):
+    ctx = mpmi.Context(0)
+    sys = mpmi.balance_bot_system(eps32=(1e30, 1e30), noise=[1e-3, 0.0, 2e-3, 1e-3] if noise else None)
+    model = mpmi.mpmi_model_pack(ctx, sys, torch.tensor(W.bb_model()[0], device="cuda"))
+    states = synth.balance_bot_states(3, seed=23)
+    if theta is not None:
+        states[:, 2] = theta
+    _against_the_many_loop_form(ctx, model, states, synth.uniform_user(3, [-5.0], [5.0], seed=24), N, H, S)
+
+
+def _against_the_many_loop_form(ctx, model, states, users, N, H, S):
     for i in range(3):
         x = torch.tensor(states[i], dtype=torch.float32, device="cuda")
-        if psi is not None:
-            x[2] = psi
         u = torch.tensor(users[i], dtype=torch.float32, device="cuda")
         fv = torch.zeros(N + 1, dtype=torch.int16, device="cuda")
         rec = mpmi.mpmi_tick(ctx, model, mpmi.tick_desc(N, H, gen=mpmi.GEN_UNIFORM, n_seg=S, seed=5, tick=i,
@@ -59,3 +77,53 @@ def test_every_first_violation_is_the_one_lane_forms(N, H, S, psi, noise):
         assert mpmi.decode_selection(rec)["n_recheck"] == N + 1
         assert torch.equal(fv, loop["first_violation"])
         assert torch.equal(rec, loop["out"])
+
+
+# features: whole sixteens, one over, one; atoms: up to 16 and more; a linear basis (D = 0 here)
+@pytest.mark.parametrize("D,n,m", [(0, 4, 2), (1, 1, 1), (15, 3, 2), (16, 2, 1), (17, 6, 3), (32, 5, 1), (33, 8, 4),
+                                   (49, 6, 2), (64, 8, 4)])
+def test_described_bases_against_a_float64_prediction(D, n, m):
+    rng = np.random.default_rng(100 * D + 10 * n + m)
+    nw, N, H, S = n + m, 333, 30, 3
+    box = [(k, 1.5, 0.0) for k in range(min(4, n))]
+    bands = dict(eps32_box=[1e30] * len(box))
+    if D:
+        atoms = [("one", 0)] + [(k, v) for k in ("var", "sin", "cos") for v in range(nw)]
+        atoms = atoms[:32] if D >= 33 else atoms[:1 + nw + nw // 2]
+        feats = [(1 + k, 0) for k in range(nw)]
+        while len(feats) < D:
+            feats.append((int(rng.integers(len(atoms))), int(rng.integers(len(atoms)))))
+        feats = feats[:D]
+        sys = mpmi.custom_system(n, m, atoms, feats, box, [-1.0] * m, [1.0] * m, **bands)
+    else:
+        atoms, feats = [("one", 0)] + [("var", k) for k in range(nw)], [(1 + k, 0) for k in range(nw)]
+        sys = mpmi.linear_system(n, m, box, [-1.0] * m, [1.0] * m)
+        for b in range(len(box)):
+            sys.eps32_box[b] = 1e30
+    K = 0.03 * rng.standard_normal((len(feats), n))
+    for j in range(min(n, len(feats))):
+        K[j, j] += 0.99
+    ctx = mpmi.Context(0)
+    model = mpmi.mpmi_model_pack(ctx, sys, torch.tensor(K, device="cuda"))
+    x = (0.4 * rng.standard_normal(n)).astype(np.float32)
+    u = rng.uniform(-1.0, 1.0, size=m).astype(np.float32)
+    cand = rng.uniform(-1.0, 1.0, size=(S, m, N)).astype(np.float32)
+    fv = torch.zeros(N + 1, dtype=torch.int16, device="cuda")
+    rec = mpmi.mpmi_tick(ctx, model, mpmi.tick_desc(N, H, gen=mpmi.GEN_EXPLICIT, n_seg=S,
+                                                    precision=mpmi.PREC_FP32_RECHECK64),
+                         torch.tensor(x, device="cuda"), torch.tensor(u, device="cuda"),
+                         cand=torch.tensor(cand, device="cuda"), first_violation=fv)
+    assert mpmi.decode_selection(rec)["n_recheck"] == N + 1
+    inputs = np.concatenate([np.broadcast_to(u[None, :, None], (S, m, 1)), cand], axis=2).astype(np.float64)
+    X = np.broadcast_to(x.astype(np.float64)[:, None], (n, N + 1))
+    want, least = np.full(N + 1, H + 1), np.inf
+    for s in range(1, H + 1):
+        w = np.concatenate([X, inputs[((s - 1) * S) // H]])
+        at = [{"one": np.ones_like, "var": lambda v: v, "sin": np.sin, "cos": np.cos}[k](w[v]) for k, v in atoms]
+        X = K.T @ np.stack([at[a] * at[b] for a, b in feats])
+        margin = np.min([1.5 - np.abs(X[k]) for k, _, _ in box], axis=0)
+        going = want == H + 1
+        least = min(least, np.min(np.abs(margin[going]), initial=np.inf))
+        want[going & ~(margin > 0)] = s
+    assert least > 1e-9, "an undecided margin"
+    assert np.array_equal(fv.cpu().numpy(), want)
