@@ -587,28 +587,31 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
 //
 // Up to 65,536 lanes are one wave per SIMD of the chip, whose step takes the
 // longer the more columns a lane forms: the most lanes that fit win, to 8.
-// Race car, H = 60, us by lanes 1 / 2 / 4 / 8: 8,193 candidates 76 / 35 / 31.5 /
-// 30; 12,289 75 / 35 / 33 / 37; 16,385 76 / 36 / 38 / 41; 32,769 75 / 37 / 42 /
-// 55.  Past that a second wave per SIMD makes two lanes slower at once (49,153:
-// 71), while three waves of the four-lane form still beat one lane (61 against
-// 76); 65,537: 78 / 97 / 81 / 102.  (FP32_RECHECK64 adds its two launches to
-// each.)  The balance bot's step is short and the publication of a workgroup
-// (15 ns each) weighs more than its columns: H = 50, 4,097 candidates 31 / 17.3 /
-// 16.7 / 18.6; 16,385 31 / 18.8 / 20 / 23; 262,145 49 / 46 / 75 / 166.  A custom
-// basis has one split form, of eight lanes (three-input car, H = 25: 10,121
-// candidates 159 / 28.6; 60,001 162 / 80; 120,001 174 / 136; level near 155,000).
+// Race car, H = 60, us by lanes 1 / 2 / 4 / 8: 8,192 candidates 75 / 32 / 27 /
+// 26; 10,001 75 / 32 / 28 / 30; 16,384 75 / 33 / 29.5 / 32; 20,001 75 / 34 / 36 /
+// 37; 32,768 75 / 36 / 38 / 46.  One more is a wave more than the SIMDs hold of
+// the two-lane form (its registers leave room for one), which then takes two
+// turns: 32,769 75 / 55 / 46 / 47; 49,152 76 / 63 / 55 / 63; 65,536 77 / 65 / 68 /
+// 79; 65,537 77 / 90 / 78 / 82.  (FP32_RECHECK64 adds its two launches to each.)
+// The balance bot's step is short and the publication of a workgroup (15 ns
+// each) weighs more than its columns: H = 50, 1,024 candidates 29 / 13.0 / 11.3 /
+// 11.9; 8,192 29.5 / 13.5 / 12.8 / 15.8; 16,384 29.5 / 14.7 / 15.1 / 19.5; 262,145
+// 44 / 43 / 71 / 133.  A custom basis has one split form, of eight lanes
+// (three-input car, H = 25: 10,121 candidates 159 / 28.6; 60,001 162 / 80; 120,001
+// 174 / 136; level near 155,000).
 static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj, bool open) {
   if (d.lanes_per_cand > 1) return d.lanes_per_cand;
   if (!open || traj || d.block > 256 || mpmi::system_noisy(sys)) return 1;
   const long long c = (long long)d.n_cand + 1;
   switch (sys.basis) {
     case MPMI_BASIS_BALANCE_BOT:
-      return c <= 4096 + 1 ? 4 : (c <= 262144 + 1 ? 2 : 1);
+      return c <= 8192 ? 4 : (c <= 262144 + 1 ? 2 : 1);
     case MPMI_BASIS_RACE_CAR:
-      if (8 * c <= 65536) return 8;
-      if (4 * c <= 65536) return 4;
-      if (2 * c <= 65536 + 64) return 2;  // 32,768 points and the user's input
-      return 4 * c <= 3 * 65536 ? 4 : 1;
+      if (c <= 8192) return 8;
+      if (c <= 16384 + 64) return 4;  // 16,384 points and the user's input
+      if (c <= 32768) return 2;
+      if (c <= 49152) return 4;
+      return c <= 65536 ? 2 : 1;
     case MPMI_BASIS_CUSTOM:
       return c <= 131072 + 1 ? 8 : 1;
     default:

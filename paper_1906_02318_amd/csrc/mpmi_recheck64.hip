@@ -22,8 +22,9 @@
 // candidate over sixteen lanes (one output component each, the step's
 // coefficients in registers), or eight when many are kept; the described bases
 // spread one over sixteen (an atom or two, four features and an output
-// component each), or run one per lane when very many are kept.  The many-loop form lists (loop, candidate, model)
-// entries and prunes by each loop's K* itself.
+// component each), or run one per lane when very many are kept.  The many-loop
+// form lists (loop, candidate, model) entries and prunes by each loop's K*
+// itself.
 #include <hip/hip_runtime.h>
 
 #include "mpmi_device.hpp"
@@ -987,8 +988,10 @@ hipError_t launch_recheck64(const mpmi_system& sys, const void* model, const mpm
     kern<<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl, capacity, gate);
   } else {
     const bool wide = sys.basis == MPMI_BASIS_CUSTOM && sys.dim > 32;
-    auto kern = small ? (noisy ? described_kernel<kSmallTrackDeg, true>(wide) : described_kernel<kSmallTrackDeg, false>(wide))
-                      : (noisy ? described_kernel<kMaxHarm, true>(wide) : described_kernel<kMaxHarm, false>(wide));
+    auto kern = small && noisy ? described_kernel<kSmallTrackDeg, true>(wide)
+                : small        ? described_kernel<kSmallTrackDeg, false>(wide)
+                : noisy        ? described_kernel<kMaxHarm, true>(wide)
+                               : described_kernel<kMaxHarm, false>(wide);
     kern<<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl, capacity, gate);
   }
   return hipGetLastError();

@@ -40,7 +40,8 @@ def _dev(v):
 @pytest.mark.parametrize("prec", [mpmi.PREC_FP32, mpmi.PREC_FP32_RECHECK64], ids=["fp32", "recheck64"])
 @pytest.mark.parametrize("kind,N", [("bb", 0), ("bb", 63), ("bb", 4096), ("bb", 4097), ("bb", 262145), ("rc", 1),
                                     ("rc", 8191), ("rc", 8192), ("rc", 16383), ("rc", 16384), ("rc", 32768),
-                                    ("rc", 32900), ("rc", 49152)])
+                                    ("rc", 32900), ("rc", 49152), ("bb", 8191), ("bb", 8192), ("rc", 16448),
+                                    ("rc", 32767), ("rc", 49151), ("rc", 65535), ("rc", 65536)])
 def test_fixed_bases_take_the_same_decision_in_every_form(prec, kind, N):
     ctx = mpmi.Context(0)
     if kind == "bb":
