@@ -301,8 +301,7 @@ __device__ __forceinline__ CandResult evaluate_candidate(const ModelDev* __restr
         for (int j = 0; j < NS; ++j)
           if (j < n) __builtin_nontemporal_store(x[j], &traj[((size_t)(s - 1) * n + j) * traj_ld + c]);
       }
-      const float mg = NEAR ? min_margin_near<NS, DEG>(md, x, &near) : min_margin<NS, DEG>(md, x);
-      if (!(mg > 0.0f)) {
+      if (!step_safe<NS, DEG, NEAR>(md, x, &near)) {
         fv = s;
         break;
       }
