@@ -478,6 +478,13 @@ struct Stepper<MPMI_BASIS_RACE_CAR> {
       Tc[j] = fmaf(a, K[56 * 6 + j], K[46 * 6 + j]);
     }
   }
+  // STRAIGHT: the last row's products go straight into the state by the
+  // three-address form; with the accumulating one the compiler copies the six
+  // sums afterwards, which costs where the vector instructions bound the step
+  // (64 loops 189 against 186.6 us; 1,048,576 candidates, with step_safe, 424 to
+  // 414) and hides where states are stored (50,000 stored candidates 114.7
+  // against 116.6).
+  template <bool STRAIGHT = false>
   __device__ __forceinline__ void step(const ModelDev* __restrict__, const float4* sK, float* x) {
     // Hardware sine/cosine (argument scaled to revolutions): about 1e-6
     // absolute error for headings within a few hundred turns, well inside
@@ -513,11 +520,13 @@ struct Stepper<MPMI_BASIS_RACE_CAR> {
     const float4 a = kk[39];
     const float2 b = *reinterpret_cast<const float2*>(kk + 40);
     const float p0 = p[26];
-    // The last row as the three-address form, straight into the state: with the
-    // accumulating one the compiler copies the six sums afterwards (64 loops 189
-    // against 186.6 us; 1,048,576 candidates, with step_safe, 424 to 414).
-    x[0] = fma3(p0, a.x, y[0]); x[1] = fma3(p0, a.y, y[1]); x[2] = fma3(p0, a.z, y[2]);
-    x[3] = fma3(p0, a.w, y[3]); x[4] = fma3(p0, b.x, y[4]); x[5] = fma3(p0, b.y, y[5]);
+    if constexpr (STRAIGHT) {
+      x[0] = fma3(p0, a.x, y[0]); x[1] = fma3(p0, a.y, y[1]); x[2] = fma3(p0, a.z, y[2]);
+      x[3] = fma3(p0, a.w, y[3]); x[4] = fma3(p0, b.x, y[4]); x[5] = fma3(p0, b.y, y[5]);
+    } else {
+      x[0] = fmaf(p0, a.x, y[0]); x[1] = fmaf(p0, a.y, y[1]); x[2] = fmaf(p0, a.z, y[2]);
+      x[3] = fmaf(p0, a.w, y[3]); x[4] = fmaf(p0, b.x, y[4]); x[5] = fmaf(p0, b.y, y[5]);
+    }
   }
 };
 

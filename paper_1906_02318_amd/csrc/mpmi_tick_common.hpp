@@ -292,7 +292,8 @@ __device__ __forceinline__ CandResult evaluate_candidate(const ModelDev* __restr
         for (int j = 0; j < MS; ++j) u[j] = (j < md->m) ? cand_value(gp, md, cand, u_user, c, g, j) : 0.0f;
         stp.set_input(md, sK, u);
       }
-      stp.step(md, sK, x);
+      if constexpr (BASIS == MPMI_BASIS_RACE_CAR) stp.template step<true>(md, sK, x);
+      else stp.step(md, sK, x);
       settle_state<NS>(x);
       if (noisy) add_process_noise<NS>(md->sys.noise_sigma, nprefix, s, n, x);
       if (traj) {
