@@ -479,6 +479,20 @@ mpmi_status mpmi_tick_lifted(mpmi_ctx ctx, void* lifted, const mpmi_tick_desc* d
                    "mpmi_tick_lifted launch");
 }
 
+// Lanes per candidate of an FP32 rollout that stores its states (the same bits
+// in every form), as tick_lanes, with the stores: race car, H = 60, us by lanes
+// 1 / 2 / 4 / 8: 8,192 candidates 73 / 26.5 / 21 / 18; 16,384 73 / 28 / 22 / 24;
+// 32,768 73 / 29 / 30 / 36; 32,800 73 / 49 / 35 / 40; 65,536 73 / 52 / 49 / 62;
+// 100,000 74 / 99 / 76 / 96.  Balance bot, H = 50: 8,192 20.5 / 10.8 / 9.5 / 9.5;
+// 32,768 21 / 11.5 / 9.5 / 18; 65,536 21 / 12.5 / 17 / 46; 131,072 22 / 25 / 32 / 101.
+static int rollout_lanes(int basis, int Nc) {
+  if (basis == MPMI_BASIS_BALANCE_BOT) return Nc <= 32768 ? 4 : (Nc <= 65536 ? 2 : 1);
+  if (basis != MPMI_BASIS_RACE_CAR || Nc > 65536) return 1;
+  if (Nc <= 8192) return 8;
+  if (Nc <= 16384 + 64) return 4;  // 16,384 points and the user's input
+  return Nc <= 32768 ? 2 : 4;
+}
+
 mpmi_status rollout_batch(mpmi_ctx ctx, const void* model, int32_t precision, const float* x0, const float* cand,
                           int32_t Nc, int32_t S, int32_t H, float* traj, int64_t traj_ld, void* stream) {
   if (!ctx) return MPMI_EINVAL;
@@ -498,6 +512,11 @@ mpmi_status rollout_batch(mpmi_ctx ctx, const void* model, int32_t precision, co
     return check_hip(ctx, mpmi::launch_rollout_bf16(model, Nc, S, H, x0, cand, traj, traj_ld, (hipStream_t)stream),
                      "rollout_batch (BF16X3) launch");
   }
+  const int lanes = rollout_lanes(sys.basis, Nc);
+  if (lanes > 1)
+    return check_hip(ctx, mpmi::launch_rollout_split(sys.basis, lanes, model, Nc, S, H, x0, cand, traj, traj_ld,
+                                                     (hipStream_t)stream),
+                     "rollout_batch launch");
   return check_hip(ctx, mpmi::launch_rollout(sys.basis, model, Nc, S, H, x0, cand, traj, traj_ld, (hipStream_t)stream),
                    "rollout_batch launch");
 }

@@ -60,6 +60,9 @@ hipError_t launch_multi_recheck64(const mpmi_loop_desc* loops, const void* model
                                   void* slots, uint64_t* ticks, void* recheck, int n_loops, int grid, hipStream_t st);
 hipError_t launch_rollout(int basis, const void* model, int Nc, int S, int H, const float* x0,
                           const float* cand, float* traj, long long traj_ld, hipStream_t st);
+// The latency form, 2, 4 or 8 lanes per candidate (race car and balance bot).
+hipError_t launch_rollout_split(int basis, int split, const void* model, int Nc, int S, int H, const float* x0,
+                                const float* cand, float* traj, long long traj_ld, hipStream_t st);
 hipError_t launch_mask(int basis, const void* model, int Nc, int H, const float* traj, long long traj_ld,
                        int16_t* fv, float* mm, uint32_t* near_bits, hipStream_t st);
 hipError_t launch_select(const void* model, int Nc, int S, int H, const float* cand, const int16_t* fv,

@@ -143,6 +143,56 @@ struct SplitRows {
   }
 };
 
+// This lane's columns of the next state, in the one-lane kernel's operation
+// order, so the two give bit-identical states: race car as the feature sum,
+// balance bot nested.
+template <int BASIS, int J>
+__device__ __forceinline__ void split_step(const SplitFold<BASIS, J>& F, const SplitRows<BASIS, J>& Kr, const float* x,
+                                           float (&y)[J]) {
+  constexpr int NS = Dims<BASIS>::N;
+  if constexpr (BASIS == MPMI_BASIS_RACE_CAR) {
+    const float sp = __sinf(x[2]), cp = __cosf(x[2]);
+#pragma unroll
+    for (int jj = 0; jj < J; ++jj) {
+      float v = fmaf(F.Tc[jj], cp, fmaf(F.Ts[jj], sp, F.cu[jj]));
+#pragma unroll
+      for (int k = 0; k < NS; ++k) v = fmaf(F.L[k][jj], x[k], v);
+      y[jj] = v;
+    }
+    int q = 0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+#pragma unroll
+      for (int l = k; l < NS; ++l, ++q) {
+        const float p = x[k] * x[l];
+#pragma unroll
+        for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(p, Kr.q[q][jj], y[jj]);
+      }
+    const float tp[6] = {sp * x[3], sp * x[4], sp * x[5], cp * x[3], cp * x[4], cp * x[5]};
+#pragma unroll
+    for (int r = 0; r < 6; ++r)
+#pragma unroll
+      for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(tp[r], Kr.t[r][jj], y[jj]);
+  } else {
+    // y = c + sum_k x_k (L_k + sum_{l >= k} Q_kl x_l) per output column.
+#pragma unroll
+    for (int jj = 0; jj < J; ++jj) y[jj] = F.cu[jj];
+    int q = 0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+      float t[J];
+#pragma unroll
+      for (int jj = 0; jj < J; ++jj) t[jj] = F.L[k][jj];
+#pragma unroll
+      for (int l = k; l < NS; ++l, ++q)
+#pragma unroll
+        for (int jj = 0; jj < J; ++jj) t[jj] = fmaf(Kr.q[q][jj], x[l], t[jj]);
+#pragma unroll
+      for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(x[k], t[jj], y[jj]);
+    }
+  }
+}
+
 // The constraint constants in registers, loaded once per launch, and the
 // safety verdict of a state.  safe(x) equals min_margin(x) > 0: every margin
 // lim - |v| is positive and none is NaN exactly when |v| < lim holds for each
@@ -388,50 +438,8 @@ tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const fl
       for (int j = 0; j < MS; ++j) u[j] = valid ? cand_value(gp, md, cand, u_user, c, gcur, j) : 0.0f;
       F.fold(sK8, colpos, u);
     }
-    // Each form in the one-lane kernel's operation order, so the two give
-    // bit-identical states: race car as the feature sum, balance bot nested.
     float y[J];
-    if constexpr (BASIS == MPMI_BASIS_RACE_CAR) {
-      const float sp = __sinf(x[2]), cp = __cosf(x[2]);
-#pragma unroll
-      for (int jj = 0; jj < J; ++jj) {
-        float v = fmaf(F.Tc[jj], cp, fmaf(F.Ts[jj], sp, F.cu[jj]));
-#pragma unroll
-        for (int k = 0; k < NS; ++k) v = fmaf(F.L[k][jj], x[k], v);
-        y[jj] = v;
-      }
-      int q = 0;
-#pragma unroll
-      for (int k = 0; k < NS; ++k)
-#pragma unroll
-        for (int l = k; l < NS; ++l, ++q) {
-          const float p = x[k] * x[l];
-#pragma unroll
-          for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(p, Kr.q[q][jj], y[jj]);
-        }
-      const float tp[6] = {sp * x[3], sp * x[4], sp * x[5], cp * x[3], cp * x[4], cp * x[5]};
-#pragma unroll
-      for (int r = 0; r < 6; ++r)
-#pragma unroll
-        for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(tp[r], Kr.t[r][jj], y[jj]);
-    } else {
-      // y = c + sum_k x_k (L_k + sum_{l >= k} Q_kl x_l) per output column.
-#pragma unroll
-      for (int jj = 0; jj < J; ++jj) y[jj] = F.cu[jj];
-      int q = 0;
-#pragma unroll
-      for (int k = 0; k < NS; ++k) {
-        float t[J];
-#pragma unroll
-        for (int jj = 0; jj < J; ++jj) t[jj] = F.L[k][jj];
-#pragma unroll
-        for (int l = k; l < NS; ++l, ++q)
-#pragma unroll
-          for (int jj = 0; jj < J; ++jj) t[jj] = fmaf(Kr.q[q][jj], x[l], t[jj]);
-#pragma unroll
-        for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(x[k], t[jj], y[jj]);
-      }
-    }
+    split_step<BASIS, J>(F, Kr, x, y);
   // The verdict of x_{s-1}, beside the step that forms x_s (the two chains
     // overlap; an unsafe x_{s-1} ends the rollout and x_s is dropped).  The
     // group's lanes hold identical states (same values, same operations).
@@ -453,6 +461,75 @@ tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const fl
   const bool near = RECHECK && ((nears >> base) & kGroup) != 0ull;
   if (fv_out && lead) fv_out[c] = (int16_t)fv;
   split_finish<MS, RECHECK>(md, gp, H, u_user, cand, slot, out, rl, lead, near, c, fv, cst);
+}
+
+// The full-horizon rollout of given candidates in the latency form: a lane
+// stores its own columns.  Race car, 60 steps, 8,192 candidates: 18 us against 73
+// with one lane per candidate.
+template <int BASIS, int SPLIT>
+__global__ void __launch_bounds__(256)
+rollout_split_kernel(const ModelDev* __restrict__ md, int Nc, int S, int H, const float* __restrict__ x0,
+                     const float* __restrict__ cand, float* __restrict__ traj, long long traj_ld) {
+  constexpr int NS = Dims<BASIS>::N, MS = Dims<BASIS>::M;
+  constexpr int J = (NS + SPLIT - 1) / SPLIT;
+  constexpr int D = (BASIS == MPMI_BASIS_RACE_CAR) ? 64 : 21;
+  __shared__ __attribute__((aligned(16))) float sK8[kSplitRows * 8];
+  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
+  const int h = gid % SPLIT;
+  const bool valid = gid / SPLIT < Nc;
+  const int c = valid ? gid / SPLIT : Nc - 1;  // lanes past the end run along and store nothing
+  const int colpos = h * SplitLayout<J>::A;
+  float x[NS], u[MS];
+#pragma unroll
+  for (int j = 0; j < NS; ++j) x[j] = x0[j];
+  auto inputs = [&](int g) {
+#pragma unroll
+    for (int j = 0; j < MS; ++j) u[j] = cand[((size_t)g * MS + j) * (size_t)Nc + c];
+  };
+  inputs(0);
+  stage_K_split<BASIS, J>(md, sK8);
+  SplitFold<BASIS, J> F;
+  F.fold(sK8, colpos, u);
+  SplitRows<BASIS, J> Kr;
+  Kr.load(sK8, D, colpos);
+  __syncthreads();
+  int nxt = (H + S - 1) / S;  // as in tick_split_kernel
+  for (int s = 1; s <= H; ++s) {
+    if (s - 1 >= nxt) {
+      const int g = ((s - 1) * S) / H;
+      nxt = ((g + 1) * H + S - 1) / S;
+      inputs(g);
+      F.fold(sK8, colpos, u);
+    }
+    float y[J];
+    split_step<BASIS, J>(F, Kr, x, y);
+    rebuild_state<NS, J, SPLIT>(y, x);
+    settle_state<NS>(x);
+#pragma unroll
+    for (int jj = 0; jj < J; ++jj) {
+      const int j = h * J + jj;
+      if (valid && j < NS) __builtin_nontemporal_store(y[jj], &traj[((size_t)(s - 1) * NS + j) * (size_t)traj_ld + c]);
+    }
+  }
+}
+
+template <int BASIS>
+static void rollout_split(int split, const ModelDev* md, int Nc, int S, int H, const float* x0, const float* cand,
+                          float* traj, long long traj_ld, hipStream_t st) {
+  const unsigned grid = (unsigned)(((long long)Nc * split + 255) / 256);
+  if (split == 2) rollout_split_kernel<BASIS, 2><<<grid, 256, 0, st>>>(md, Nc, S, H, x0, cand, traj, traj_ld);
+  else if (split == 4) rollout_split_kernel<BASIS, 4><<<grid, 256, 0, st>>>(md, Nc, S, H, x0, cand, traj, traj_ld);
+  else rollout_split_kernel<BASIS, 8><<<grid, 256, 0, st>>>(md, Nc, S, H, x0, cand, traj, traj_ld);
+}
+
+hipError_t launch_rollout_split(int basis, int split, const void* model, int Nc, int S, int H, const float* x0,
+                                const float* cand, float* traj, long long traj_ld, hipStream_t st) {
+  const ModelDev* md = (const ModelDev*)model;
+  if (basis == MPMI_BASIS_RACE_CAR)
+    rollout_split<MPMI_BASIS_RACE_CAR>(split, md, Nc, S, H, x0, cand, traj, traj_ld, st);
+  else
+    rollout_split<MPMI_BASIS_BALANCE_BOT>(split, md, Nc, S, H, x0, cand, traj, traj_ld, st);
+  return hipGetLastError();
 }
 
 // Latency form for a basis given as data: one candidate over the 8 lanes of an
