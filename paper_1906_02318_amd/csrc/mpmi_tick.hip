@@ -97,29 +97,50 @@ rollout_fp32_kernel(const ModelDev* __restrict__ md, int Nc, int S, int H, const
 // a step-by-step scan.  At most kMaskChunk - 1 steps past the first violation
 // are read and ignored.
 //
-// Bound: memory.  Of a race car's six components three carry a constraint and
-// are read: 180 of the cloud's 360 MB at 250,000 candidates and 60 steps, 50 us
-// (3.6 TB/s) against 65 for all six.  Chunks of 8, and the next chunk loaded
-// ahead of the check, gave nothing.
+// Bound: memory, and few waves the latency of a lane's chunks.  Of a race car's
+// six components three carry a constraint and are read: 180 of the cloud's 360
+// MB at 250,000 candidates and 60 steps, 37 us (4.9 TB/s) against 67 for all six
+// by one wave per 64 candidates; 1,000,000 139 against 258; 20,000 12 against 28.
+// Two parts take 36, 136 and 18 us, eight 41, 163 and 15.5.
 constexpr int kMaskChunk = 4;
 
 // NEAR: also the near-boundary bitmask (bit c % 32 of word c / 32 set when
 // some checked state of candidate c has a margin within its FP32 band), one
 // ballot per wave.  Blocks are whole waves; lanes past Nc take part in the
 // ballot only.
+//
+// A workgroup of kMaskParts waves takes 64 candidates, wave p the p-th part of
+// the horizon; the parts up to the first that holds a violation are the
+// step-by-step scan.  A wave drops the lanes that an earlier part has found
+// unsafe (what it reads of the others' finds may be old: it then scans a chunk
+// whose result is not used).
+constexpr int kMaskParts = 4;
 template <int NS, bool NEAR>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(64 * kMaskParts)
 mask_kernel(const ModelDev* __restrict__ md, int Nc, int H, const float* __restrict__ traj, long long traj_ld,
             int16_t* __restrict__ fv_out, float* __restrict__ mm_out, uint32_t* __restrict__ near_bits) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ volatile unsigned long long s_ended[kMaskParts];
+  __shared__ int s_fv[kMaskParts][64];
+  __shared__ float s_least[kMaskParts][64];
+  __shared__ unsigned long long s_near[kMaskParts];
+  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6, c = blockIdx.x * 64 + lane;
   const bool valid = c < Nc;
   const int cc = valid ? c : Nc - 1;  // lanes past the end scan a valid candidate and store nothing
   const int n = md->n;
   const int need = (md->safe.comp_mask | (md->safe.has_track ? 3 : 0)) & ((1 << n) - 1);
+  if (threadIdx.x < kMaskParts) s_ended[threadIdx.x] = 0ull;
+  __syncthreads();
+  const int span = (H + kMaskParts * kMaskChunk - 1) / (kMaskParts * kMaskChunk) * kMaskChunk;
+  const int first = 1 + part * span, last = min(H, first + span - 1);
   int fv = H + 1;
   float least = INFINITY;
   bool near = false;
-  for (int s0 = 1; s0 <= H && fv > H; s0 += kMaskChunk) {
+  unsigned long long going = ~0ull;
+  for (int s0 = first; s0 <= last; s0 += kMaskChunk) {
+#pragma unroll
+    for (int p = 0; p < kMaskParts - 1; ++p)
+      if (p < part) going &= ~s_ended[p];
+    if (going == 0ull) break;
     float x[kMaskChunk][NS];
     // The components that carry a constraint, the others zero (no margin
     // reads them).  A step past the horizon rereads the last one (never
@@ -136,15 +157,35 @@ mask_kernel(const ModelDev* __restrict__ md, int Nc, int H, const float* __restr
         for (int k = 0; k < kMaskChunk; ++k) x[k][j] = 0.0f;
       }
     }
+    if ((going >> lane) & 1ull) {
 #pragma unroll
-    for (int k = 0; k < kMaskChunk; ++k) {
-      if (s0 + k > H) break;
-      const float mg = NEAR ? min_margin_near<NS>(md, x[k], &near) : min_margin<NS>(md, x[k]);
-      least = (mg != mg) ? mg : fminf(least, mg);
-      if (!(mg > 0.0f)) {
-        fv = s0 + k;
-        break;
+      for (int k = 0; k < kMaskChunk; ++k) {
+        if (s0 + k > last) break;
+        const float mg = NEAR ? min_margin_near<NS>(md, x[k], &near) : min_margin<NS>(md, x[k]);
+        least = (mg != mg) ? mg : fminf(least, mg);
+        if (!(mg > 0.0f)) {
+          fv = s0 + k;
+          break;
+        }
       }
+    }
+    const unsigned long long ended = __ballot(fv <= H);
+    going &= ~ended;
+    if (lane == 0) s_ended[part] = ended;
+  }
+  s_fv[part][lane] = fv;
+  s_least[part][lane] = least;
+  const unsigned long long nearest = __ballot(near);
+  if (lane == 0) s_near[part] = nearest;
+  __syncthreads();
+  if (part > 0) return;
+#pragma unroll
+  for (int p = 1; p < kMaskParts; ++p) {
+    if (fv > H) {
+      const float l = s_least[p][lane];
+      least = (l != l) ? l : fminf(least, l);
+      near |= (s_near[p] >> lane) & 1ull;
+      fv = s_fv[p][lane];
     }
   }
   if (valid) {
@@ -153,7 +194,6 @@ mask_kernel(const ModelDev* __restrict__ md, int Nc, int H, const float* __restr
   }
   if (NEAR) {
     const unsigned long long b = __ballot(valid && near);
-    const int lane = threadIdx.x & 63;
     const int c0 = c - lane;
     if (lane == 0 && c0 < Nc) near_bits[c0 >> 5] = (uint32_t)b;
     if (lane == 32 && c0 + 32 < Nc) near_bits[(c0 >> 5) + 1] = (uint32_t)(b >> 32);
@@ -495,27 +535,26 @@ hipError_t launch_rollout(int basis, const void* model, int Nc, int S, int H, co
 }
 
 template <int NS>
-static void mask_dispatch(unsigned grid, int block, hipStream_t st, const ModelDev* md, int Nc, int H,
-                          const float* traj, long long traj_ld, int16_t* fv, float* mm, uint32_t* nb) {
-  if (nb) mask_kernel<NS, true><<<grid, block, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
-  else mask_kernel<NS, false><<<grid, block, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
+static void mask_dispatch(hipStream_t st, const ModelDev* md, int Nc, int H, const float* traj, long long traj_ld,
+                          int16_t* fv, float* mm, uint32_t* nb) {
+  const unsigned grid = blocks_for(Nc, 64);
+  if (nb) mask_kernel<NS, true><<<grid, 64 * kMaskParts, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
+  else mask_kernel<NS, false><<<grid, 64 * kMaskParts, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
 }
 
 hipError_t launch_mask(int basis, const void* model, int Nc, int H, const float* traj, long long traj_ld,
                        int16_t* fv, float* mm, uint32_t* near_bits, hipStream_t st) {
-  const int block = 256;
-  const unsigned grid = blocks_for(Nc, block);
   const ModelDev* md = (const ModelDev*)model;
   switch (basis) {
     case MPMI_BASIS_LINEAR:
     case MPMI_BASIS_CUSTOM:
-      mask_dispatch<MPMI_MAX_STATE>(grid, block, st, md, Nc, H, traj, traj_ld, fv, mm, near_bits);
+      mask_dispatch<MPMI_MAX_STATE>(st, md, Nc, H, traj, traj_ld, fv, mm, near_bits);
       break;
     case MPMI_BASIS_BALANCE_BOT:
-      mask_dispatch<4>(grid, block, st, md, Nc, H, traj, traj_ld, fv, mm, near_bits);
+      mask_dispatch<4>(st, md, Nc, H, traj, traj_ld, fv, mm, near_bits);
       break;
     default:
-      mask_dispatch<6>(grid, block, st, md, Nc, H, traj, traj_ld, fv, mm, near_bits);
+      mask_dispatch<6>(st, md, Nc, H, traj, traj_ld, fv, mm, near_bits);
       break;
   }
   return hipGetLastError();
