@@ -222,7 +222,7 @@ lifted_prologue_kernel(const LiftedDev* __restrict__ ld, int H, int hpad, const 
 // each candidate's first violation, some after it).
 // ---------------------------------------------------------------------------
 template <int BASIS, int DEG, bool TRAJ>
-__global__ void __launch_bounds__(kLiftBlock)
+__global__ void __launch_bounds__(kLiftBlock, 4)
 lifted_tick_kernel(const LiftedDev* __restrict__ ld, GenParams gp, int H, int hpad,
                    const float* __restrict__ u_user, const float* __restrict__ cand, const float* __restrict__ Qt,
                    Slot* __restrict__ slot, mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out,
@@ -296,25 +296,55 @@ lifted_tick_kernel(const LiftedDev* __restrict__ ld, GenParams gp, int H, int hp
       // back to back), then the checks: one tile's MFMA latency overlaps the
       // next tile's issue and the checks of the tiles before it.
       f32x4_t acc[4], acc1[4];
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
+      auto products = [&](int ct) {
         acc[ct] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        acc1[ct] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        if (dead & (1u << ct)) continue;  // uniform
 #pragma unroll
         for (int i = 0; i < KC; ++i)
           acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[0][i], B[ct][i], acc[ct], 0, 0, 0);
         if constexpr (TRAJ) {
+          acc1[ct] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
           for (int i = 0; i < KC; ++i)
             acc1[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[G - 1][i], B[ct][i], acc1[ct], 0, 0, 0);
         }
-      }
+      };
+      // Lanes whose state of each tile is outside the safe set: min_margin > 0
+      // by a comparison into a lane mask each, the constraints by uniform
+      // branches around the tiles.
+      unsigned long long u[4] = {0, 0, 0, 0};
+      auto outside = [&](auto live) {
+        if (sc.has_track) {
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        if (dead & (1u << ct)) continue;  // uniform
-        const float x4[4] = {acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3]};
-        if constexpr (TRAJ) {
+          for (int ct = 0; ct < 4; ++ct) {
+            if (!live(ct)) continue;
+            const float xy[2] = {acc[ct][0], acc[ct][1]};
+            float rho;
+            const float rc = track_centre<DEG>(&sc, xy, &rho);
+            u[ct] |= __builtin_amdgcn_ballot_w64(!(fabsf(rho - rc) < sc.trk_lim));
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (!((sc.comp_mask >> k) & 1)) continue;
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct)
+            if (live(ct)) u[ct] |= __builtin_amdgcn_ballot_w64(!(fabsf(acc[ct][k]) < sc.comp_lim[k]));
+        }
+      };
+      if (dead == 0u) {  // uniform, the usual case
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) products(ct);
+        outside([](int) { return true; });
+      } else {
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+          if (!(dead & (1u << ct))) products(ct);
+        outside([&](int ct) { return !(dead & (1u << ct)); });
+      }
+      if constexpr (TRAJ) {
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) {
+          if (dead & (1u << ct)) continue;  // uniform
           const int c = wbase + 16 * ct + col;
           if (s <= H && c < Nc) {
             const float v8[8] = {acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3],
@@ -327,14 +357,16 @@ lifted_tick_kernel(const LiftedDev* __restrict__ ld, GenParams gp, int H, int hp
             }
           }
         }
-        const bool unsafe = !all_safe_of<4, DEG>(&sc, x4);
-        fvm[ct] = (s <= H && unsafe) ? min(fvm[ct], s) : fvm[ct];
       }
+      const unsigned long long in = __builtin_amdgcn_ballot_w64(s <= H);
+      if (((u[0] | u[1] | u[2] | u[3]) & in) != 0ull) {
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) {
-        const unsigned long long b = __ballot(fvm[ct] <= H);
-        const unsigned int f16 = (unsigned int)((b | (b >> 16) | (b >> 32) | (b >> 48)) & 0xffffull);
-        if ((f16 | inval[ct]) == 0xffffu) dead |= 1u << ct;
+        for (int ct = 0; ct < 4; ++ct) {
+          if (((u[ct] & in) >> lane) & 1ull) fvm[ct] = min(fvm[ct], s);
+          const unsigned long long b = __builtin_amdgcn_ballot_w64(fvm[ct] <= H);
+          const unsigned int f16 = (unsigned int)((b | (b >> 16) | (b >> 32) | (b >> 48)) & 0xffffull);
+          if ((f16 | inval[ct]) == 0xffffu) dead |= 1u << ct;
+        }
       }
     }
     // first violation of each candidate: least over its four lanes; lane l
