@@ -475,7 +475,7 @@ mpmi_status mpmi_tick_lifted(mpmi_ctx ctx, void* lifted, const mpmi_tick_desc* d
     return fail(ctx, MPMI_EINVAL, "traj_ld=%lld below N+1=%d", (long long)traj_ld, desc->n_cand + 1);
   void* slot = (char*)ctx->slots + (size_t)desc->loop * mpmi::slot_bytes();
   return check_hip(ctx, mpmi::launch_tick_lifted(sys, lifted, it->second.h_max, *desc, x_t, u_user, cand, slot, out,
-                                                 first_violation, traj, traj ? traj_ld : 0, 4, (hipStream_t)stream),
+                                                 first_violation, traj, traj ? traj_ld : 0, 8, (hipStream_t)stream),
                    "mpmi_tick_lifted launch");
 }
 

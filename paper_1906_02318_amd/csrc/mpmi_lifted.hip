@@ -220,6 +220,13 @@ lifted_prologue_kernel(const LiftedDev* __restrict__ ld, int H, int hpad, const 
 // ... and publishes its arg-min keys once.  TRAJ also computes slots 4..7 and
 // stores the predicted states of the steps it evaluates (every step up to
 // each candidate's first violation, some after it).
+//
+// Bound: issue, the matrix cores 33 us and the vector instructions 46 us (70 of
+// 85 per row of tiles are the checks) of 93 at 1,048,576 candidates and 60
+// steps.  With the products in accumulation registers, a branch and a fold of
+// the dead tiles per tile and each candidate's input functions formed by four
+// lanes it was 150; four workgroups per compute unit instead of the launch's
+// eight take 99.5, ten 93, one per pass 111.
 // ---------------------------------------------------------------------------
 template <int BASIS, int DEG, bool TRAJ>
 __global__ void __launch_bounds__(kLiftBlock, 4)
@@ -229,6 +236,7 @@ lifted_tick_kernel(const LiftedDev* __restrict__ ld, GenParams gp, int H, int hp
                    float* __restrict__ traj, long long traj_ld) {
   constexpr int KP = LiftShape<BASIS>::KP, KC = KP / 4, MS = Dims<BASIS>::M, G = TRAJ ? 2 : 1;
   extern __shared__ float sQ[];  // [G][hpad][KP][4]
+  __shared__ float4 sG[kLiftBlock / 64][64];
   const ModelDev* __restrict__ md = &ld->md;
   // The constraint constants held in registers for the whole launch (a call
   // per output tile re-fetching them by scalar loads stalled on each fetch).
@@ -257,32 +265,32 @@ lifted_tick_kernel(const LiftedDev* __restrict__ ld, GenParams gp, int H, int hp
     float own_u[MS];
     int fvm[4];
     unsigned int dead = 0, inval[4];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const int c = wbase + 16 * ct + col;
+    // One candidate's input functions per lane, handed round through LDS four
+    // at a time: the B operand i of tile ct is function 4 i + quarter of
+    // candidate 16 ct + col.  (A wave's LDS accesses are in order.)
+    {
+      const int c = wbase + lane;
       const bool valid = c < Nc;
-      float u[MS], g[KP];
+      float g[KP];
 #pragma unroll
-      for (int j = 0; j < MS; ++j) u[j] = (valid && j < md->m) ? cand_value(gp, md, cand, u_user, c, 0, j) : 0.0f;
-      g_eval<BASIS>(u, md->m, g);
+      for (int j = 0; j < MS; ++j) own_u[j] = (valid && j < md->m) ? cand_value(gp, md, cand, u_user, c, 0, j) : 0.0f;
+      g_eval<BASIS>(own_u, md->m, g);
 #pragma unroll
       for (int i = 0; i < KC; ++i) {
-        // register values: the selection stays a chain of selects instead of
-        // becoming an indexed scratch load of g
-        float g0 = g[4 * i], g1 = g[4 * i + 1], g2 = g[4 * i + 2], g3 = g[4 * i + 3];
-        asm volatile("" : "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3));
-        float v = quarter == 1 ? g1 : g0;
-        v = quarter == 2 ? g2 : v;
-        v = quarter == 3 ? g3 : v;
-        B[ct][i] = v;
-      }
-      if (quarter == ct) {
+        asm volatile("" ::: "memory");
+        sG[wave][lane] = make_float4(g[4 * i], g[4 * i + 1], g[4 * i + 2], g[4 * i + 3]);
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < MS; ++j) own_u[j] = u[j];
+        for (int ct = 0; ct < 4; ++ct)
+          B[ct][i] = reinterpret_cast<const float*>(&sG[wave][16 * ct + col])[quarter];
       }
+      asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) {
       fvm[ct] = H + 1;
-      const unsigned long long b = __ballot(!valid);
-      inval[ct] = (unsigned int)((b | (b >> 16) | (b >> 32) | (b >> 48)) & 0xffffull);
+      const int past = wbase + 16 * ct + 16 - Nc;  // lanes of the tile past the last candidate
+      inval[ct] = past <= 0 ? 0u : past >= 16 ? 0xffffu : (0xffffu << (16 - past)) & 0xffffu;
       if (inval[ct] == 0xffffu) dead |= 1u << ct;
     }
     for (int rt = 0; rt < nrt && dead != 0xfu; ++rt) {
