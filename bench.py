@@ -427,9 +427,10 @@ def run_trajectory_store(st: dict, reps: int = 10):
             res["separable_calls_1m"]["ms_total"] = float(sum(np.median(v) for v in ph.values()))
             res["separable_calls_1m"]["ms_fused_tick"] = times["decision"]
             res["separable_calls_1m"]["same_selection"] = bool(sel_s == sel_f)
-            # safe_mask needs the states up to each first violation: the
-            # executed units' bytes, against the read ceiling of its pattern
-            mask_gbs = wbytes / (float(np.median(ph["safe_mask"])) * 1e-3) / 1e9
+            # safe_mask needs, up to each first violation, the components that
+            # carry a constraint (x, y and v_y of six): those bytes, against
+            # the read ceiling of its pattern
+            mask_gbs = units * 3 * 4 / (float(np.median(ph["safe_mask"])) * 1e-3) / 1e9
             res["separable_calls_1m"]["safe_mask_read_GB_s"] = mask_gbs
             res["separable_calls_1m"]["safe_mask_read_frac"] = mask_gbs / rceil["pattern_GB_s"]
             del cand
@@ -580,7 +581,7 @@ def run_mlp_training(batch: int = 4096, steps: int = 50, warmup: int = 5):
             "mfma_frac": tflops / PEAK_BF16_MFMA_TFLOPS,
             "note": (f"11 dense products of at most {batch} x 256 x 256 plus loss, split-K reductions and "
                      "Adam; " + ("launch- and latency-bound" if batch <= 8192 else
-                                 "HBM-bound (37-51 flops per byte moved)") + "; kernel times in profiles/")}
+                                 "bound by weight and activation reads and the weight-gradient operands") + "; kernel times in profiles/")}
 
 
 def run_plain_vs_learned(n_ticks: int = 500, warmup: int = 20):

@@ -467,8 +467,8 @@ __device__ __forceinline__ RcLane64<DEG> rc_lane64(const Model64* __restrict__ m
 //
 // Bound: one wave's chain, about 770 cycles per step against about 1400 for
 // the 8-lane form (its coefficients come from LDS at every step, and its
-// exchange goes through it): a 60-step tick of 16,384 candidates that keeps a
-// few hundred takes 70 us, 85 us by the 8-lane form (43 us with none kept).
+// exchange goes through it): keeping a few hundred adds 26 us to a 60-step tick,
+// 41 us by the 8-lane form.
 // Of its step neither the column's terms, the exit nor 1 / rho shows when it is
 // taken out; the heading's series and its exchange do.
 template <int DEG, bool NOISE, bool FAR>
@@ -732,8 +732,8 @@ constexpr int kRowLds = kRowW + MPMI_MAX_ATOMS + 1;
 // Bound: one wave's chain per step, through LDS twice (atoms, products), a sine
 // and a cosine per lane, and one instruction per feature.  One candidate per
 // lane pays the sine and cosine of every atom one after the other, and every
-// feature for every component.  A balance-bot tick of 10,000 candidates, 50
-// steps, that keeps many of them: 183 to 46 us (24 us with none kept).
+// feature for every component.  Keeping many of 10,000 adds 22 us to a 50-step
+// balance-bot tick, 160 us that way.
 template <int DEG, int KD, bool NOISE>
 __device__ __forceinline__ int evaluate64_row(const ModelDev* __restrict__ md, const GenParams& gp, int H,
                                               const float* __restrict__ x_t, const float* __restrict__ u_user,
