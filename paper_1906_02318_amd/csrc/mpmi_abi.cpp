@@ -21,7 +21,8 @@
 struct mpmi_ctx_s {
   int device = 0;
   void* slots = nullptr;       // MPMI_MAX_LOOPS selection slots
-  void* fit_work = nullptr;    // fit partial sums, totals and info
+  void* fit_work = nullptr;    // fit partial sums and totals
+  mpmi::FitInfo* fit_info = nullptr;  // what a fit reports: pinned host memory, written by its solve
   void* recheck = nullptr;     // BF16X3 recheck list (count + indices)
   std::unordered_map<const void*, mpmi_system> models;  // packed models, by device address
   struct Lifted {
@@ -264,6 +265,7 @@ mpmi_status mpmi_create(mpmi_ctx* out, int32_t device) {
   const size_t slot_bytes = (size_t)MPMI_MAX_LOOPS * mpmi::slot_bytes();
   if (hipMalloc(&ctx->slots, slot_bytes) != hipSuccess ||
       hipMalloc(&ctx->fit_work, mpmi::fit_workspace_bytes()) != hipSuccess ||
+      hipHostMalloc((void**)&ctx->fit_info, sizeof(mpmi::FitInfo), hipHostMallocMapped) != hipSuccess ||
       hipMalloc(&ctx->recheck, mpmi::recheck_bytes(mpmi::kRecheckCapacity)) != hipSuccess) {
     mpmi_destroy(ctx);
     return MPMI_ENOMEM;
@@ -288,6 +290,7 @@ void mpmi_destroy(mpmi_ctx ctx) {
   if (!ctx) return;
   if (ctx->slots) (void)hipFree(ctx->slots);
   if (ctx->fit_work) (void)hipFree(ctx->fit_work);
+  if (ctx->fit_info) (void)hipHostFree(ctx->fit_info);
   if (ctx->recheck) (void)hipFree(ctx->recheck);
   delete ctx;
 }
@@ -326,13 +329,11 @@ mpmi_status koopman_fit(mpmi_ctx ctx, const mpmi_system* sys, const double* X, c
   if (T > (int64_t)1 << 40) return fail(ctx, MPMI_EINVAL, "T=%lld too large", (long long)T);
   if (!(ridge >= 0.0)) return fail(ctx, MPMI_EINVAL, "ridge must be >= 0");
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = mpmi::launch_fit(*sys, D, X, U, Y, T, ridge, K_out, ctx->fit_work, st);
+  hipError_t e = mpmi::launch_fit(*sys, D, X, U, Y, T, ridge, K_out, ctx->fit_work, ctx->fit_info, st);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit launch: %s", hipGetErrorString(e));
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit: %s", hipGetErrorString(e));
-  mpmi::FitInfo info;
-  e = hipMemcpy(&info, (char*)ctx->fit_work + mpmi::fit_info_offset(), sizeof info, hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit readback: %s", hipGetErrorString(e));
+  const mpmi::FitInfo info = *ctx->fit_info;  // complete with the stream: no copy of its own (10 us a call)
   if (cond_out) *cond_out = condition(info);
   if (info.status != MPMI_OK)
     return fail(ctx, MPMI_ESINGULAR, "scaled Gram matrix is not numerically positive definite");
@@ -353,13 +354,11 @@ mpmi_status koopman_fit_lifted(mpmi_ctx ctx, const mpmi_system* sys, const doubl
   if (T > (int64_t)1 << 40) return fail(ctx, MPMI_EINVAL, "T=%lld too large", (long long)T);
   if (!(ridge >= 0.0)) return fail(ctx, MPMI_EINVAL, "ridge must be >= 0");
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = mpmi::launch_fit_lifted(*sys, D, X, U, Y, T, ridge, K_out, ctx->fit_work, st);
+  hipError_t e = mpmi::launch_fit_lifted(*sys, D, X, U, Y, T, ridge, K_out, ctx->fit_work, ctx->fit_info, st);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit_lifted launch: %s", hipGetErrorString(e));
   e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit_lifted: %s", hipGetErrorString(e));
-  mpmi::FitInfo info;
-  e = hipMemcpy(&info, (char*)ctx->fit_work + mpmi::fit_info_offset(), sizeof info, hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return fail(ctx, MPMI_EDEVICE, "koopman_fit_lifted readback: %s", hipGetErrorString(e));
+  const mpmi::FitInfo info = *ctx->fit_info;
   if (cond_out) *cond_out = condition(info);
   if (info.status != MPMI_OK)
     return fail(ctx, MPMI_ESINGULAR, "scaled Gram matrix is not numerically positive definite");

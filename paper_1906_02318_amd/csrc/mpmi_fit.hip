@@ -626,11 +626,9 @@ solve_kernel(int ny, int D, long long T, double ridge, const double* __restrict_
   }
 }
 
-// Workspace: partial sums, totals, then the info record (256 bytes at
-// fit_info_offset()).
+// Workspace: partial sums, then totals.
 constexpr int kFitColsMax = 2 * MPMI_MAX_DIM;  // the lifted operator's D + D columns
-size_t fit_info_offset() { return (size_t)(kFitBlocks + 1) * MPMI_MAX_DIM * kFitColsMax * sizeof(double); }
-size_t fit_workspace_bytes() { return fit_info_offset() + 256; }
+size_t fit_workspace_bytes() { return (size_t)(kFitBlocks + 1) * MPMI_MAX_DIM * kFitColsMax * sizeof(double); }
 
 // One least-squares solve: targets Y (ny = n), or psi(Y, U) for the lifted
 // operator (ny = dim).  Race car, T = 50,000, one MI355X: Gram 22 us (29 with
@@ -641,13 +639,13 @@ size_t fit_workspace_bytes() { return fit_info_offset() + 256; }
 // order of the sums.
 template <bool LIFTED>
 static hipError_t fit_columns(const mpmi_system& sys, int dim, int ny, const double* X, const double* U,
-                              const double* Y, int64_t T, double ridge, double* K_out, void* work, hipStream_t st) {
+                              const double* Y, int64_t T, double ridge, double* K_out, void* work, FitInfo* info,
+                              hipStream_t st) {
   const int E = dim * (dim + ny);
   long long ntiles = (T + kFitRows - 1) / kFitRows;
   const int nparts = (int)(ntiles < kFitBlocks ? ntiles : kFitBlocks);
   double* part = (double*)work;
   double* tot = part + (size_t)kFitBlocks * MPMI_MAX_DIM * kFitColsMax;
-  FitInfo* info = (FitInfo*)((char*)work + fit_info_offset());
   gram_kernel<LIFTED><<<nparts, GramShape<LIFTED>::kThreads, 0, st>>>(sys, dim, ny, X, U, Y, (long long)T, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -659,8 +657,8 @@ static hipError_t fit_columns(const mpmi_system& sys, int dim, int ny, const dou
 }
 
 hipError_t launch_fit(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
-                      int64_t T, double ridge, double* K_out, void* work, hipStream_t st) {
-  return fit_columns<false>(sys, dim, sys.n_state, X, U, Y, T, ridge, K_out, work, st);
+                      int64_t T, double ridge, double* K_out, void* work, FitInfo* info, hipStream_t st) {
+  return fit_columns<false>(sys, dim, sys.n_state, X, U, Y, T, ridge, K_out, work, info, st);
 }
 
 // The lifted operator K (dim x dim, targets psi(Y_t, U_t)): the same scaled
@@ -668,8 +666,8 @@ hipError_t launch_fit(const mpmi_system& sys, int dim, const double* X, const do
 // and one factorisation.  It was solved eight columns at a time, each chunk
 // forming the Gram matrix and its factor again.
 hipError_t launch_fit_lifted(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
-                             int64_t T, double ridge, double* K_out, void* work, hipStream_t st) {
-  return fit_columns<true>(sys, dim, dim, X, U, Y, T, ridge, K_out, work, st);
+                             int64_t T, double ridge, double* K_out, void* work, FitInfo* info, hipStream_t st) {
+  return fit_columns<true>(sys, dim, dim, X, U, Y, T, ridge, K_out, work, info, st);
 }
 
 }  // namespace mpmi

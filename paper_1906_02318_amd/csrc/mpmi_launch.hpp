@@ -72,7 +72,6 @@ hipError_t launch_gen(const void* model, const mpmi_tick_desc& d, const float* u
 
 // Koopman fit (FP64): Gram accumulation, reduction, Cholesky solve.
 size_t fit_workspace_bytes();
-size_t fit_info_offset();  // FitInfo of the last solve
 // Status of a solve and the largest eigenvalues of the scaled Gram matrix and
 // of its inverse; the condition number of the scaled data is the square root
 // of their product.
@@ -82,10 +81,10 @@ struct FitInfo {
   double lmax, lmin_inv;
 };
 hipError_t launch_fit(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
-                      int64_t T, double ridge, double* K_out, void* work, hipStream_t st);
+                      int64_t T, double ridge, double* K_out, void* work, FitInfo* info, hipStream_t st);
 // Lifted operator (dim x dim) with targets psi(Y_t, U_t).
 hipError_t launch_fit_lifted(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
-                             int64_t T, double ridge, double* K_out, void* work, hipStream_t st);
+                             int64_t T, double ridge, double* K_out, void* work, FitInfo* info, hipStream_t st);
 
 // Basis selection (mpmi_select.hip): workspace bytes for n_gamma penalties,
 // and the synchronous selection.
