@@ -607,10 +607,10 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
 // longer the more columns a lane forms: the most lanes that fit win, to 8.
 // Race car, H = 60, us by lanes 1 / 2 / 4 / 8: 8,192 candidates 75 / 32 / 27 /
 // 26; 10,001 75 / 32 / 28 / 30; 16,384 75 / 33 / 29.5 / 32; 20,001 75 / 34 / 36 /
-// 37; 32,768 75 / 36 / 38 / 46.  One more is a wave more than the SIMDs hold of
-// the two-lane form (its registers leave room for one), which then takes two
-// turns: 32,769 75 / 55 / 46 / 47; 49,152 76 / 63 / 55 / 63; 65,536 77 / 65 / 68 /
-// 79; 65,537 77 / 90 / 78 / 82.  (FP32_RECHECK64 adds its two launches to each.)
+// 37; 32,768 75 / 36 / 38 / 46.  One more is a wave more than the SIMDs hold of the
+// two-lane form at its ease, and its tighter instance takes over: 32,769 75 / 40 /
+// 46 / 47; 49,152 76 / 50 / 55 / 63; 65,536 77 / 53 / 68 / 79; 65,537, a third wave,
+// 77 / 90 / 78 / 82.  (FP32_RECHECK64 adds its two launches to each.)
 // The balance bot's step is short and the publication of a workgroup (15 ns
 // each) weighs more than its columns: H = 50, 1,024 candidates 29 / 13.0 / 11.3 /
 // 11.9; 8,192 29.5 / 13.5 / 12.8 / 15.8; 16,384 29.5 / 14.7 / 15.1 / 19.5; 262,145
@@ -627,8 +627,6 @@ static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj
     case MPMI_BASIS_RACE_CAR:
       if (c <= 8192) return 8;
       if (c <= 16384 + 64) return 4;  // 16,384 points and the user's input
-      if (c <= 32768) return 2;
-      if (c <= 49152) return 4;
       return c <= 65536 ? 2 : 1;
     case MPMI_BASIS_CUSTOM:
       return c <= 131072 + 1 ? 8 : 1;

@@ -339,8 +339,14 @@ __device__ __forceinline__ void split_finish(const ModelDev* __restrict__ md, co
 // GATED (the fallback after a proposal tick): nothing to do if the gate
 // selection already found a safe candidate; an instance of its own, since the
 // test would hold up the other loads of every launch.
-template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED>
-__global__ void __launch_bounds__(256)
+//
+// WAVES: waves per SIMD to leave room for.  The race car's two-lane form holds
+// three columns of K and takes more than half the registers; an instance with
+// room for two waves (19 to 27 values in scratch, three loads of them a step)
+// serves ticks of more than one: 32,769 candidates 40 us against 53 in two turns,
+// 65,536 52.5 against 64; 32,768, one wave each, 40 against 34.6.
+template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED, int WAVES>
+__global__ void __launch_bounds__(256, WAVES)
 tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
                   const float* __restrict__ u_user, const float* __restrict__ cand, Slot* __restrict__ slot,
                   mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out, RecheckList* __restrict__ rl,
@@ -736,13 +742,17 @@ struct SplitLaunch {
   const mpmi_selection* gate;
 };
 
-template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED>
+template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED, int WAVES = 1>
 static void split_launch(const SplitLaunch& a) {
-  tick_split_kernel<BASIS, SPLIT, DEG, TRACK, RECHECK, GATED><<<a.grid, a.block, 0, a.st>>>(
+  tick_split_kernel<BASIS, SPLIT, DEG, TRACK, RECHECK, GATED, WAVES><<<a.grid, a.block, 0, a.st>>>(
       a.md, a.gp, a.H, a.x_t, a.u_user, a.cand, a.slot, a.out, a.fv, a.rl, a.gate);
 }
 template <int BASIS, int DEG, bool TRACK, bool RECHECK, bool GATED>
 static void split_lanes(const SplitLaunch& a) {
+  if constexpr (BASIS == MPMI_BASIS_RACE_CAR) {
+    if (a.split == 2 && (long long)a.grid * a.block > 64ll * 4 * device_cu_count())
+      return split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED, 2>(a);
+  }
   if (a.split == 2) split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED>(a);
   else if (a.split == 4) split_launch<BASIS, 4, DEG, TRACK, RECHECK, GATED>(a);
   else split_launch<BASIS, 8, DEG, TRACK, RECHECK, GATED>(a);
