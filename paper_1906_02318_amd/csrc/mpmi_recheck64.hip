@@ -308,10 +308,11 @@ __device__ int evaluate64(const ModelDev* __restrict__ md, const double* __restr
 // group exchanges the six new components, and every lane then holds the same
 // state (the same bits, so the same verdict and the same exit step).  Lanes 6
 // and 7 repeat column 5.  The heading's sine and cosine, the noise draws and
-// the track margin are formed by every lane; lane j tests component j's box.  Returns the first violation (1..H, or
-// H + 1).
-
-template <int DEG>
+// the track margin are formed by every lane; lane j tests component j's box.
+// Any heading is taken (sincos_rr64).  Returns the first violation (1..H, or
+// H + 1).  NOISE: the model carries process noise; tested at run time, the
+// draws' code takes the registers that keep the kernel out of scratch.
+template <int DEG, bool NOISE>
 __device__ int evaluate64_rc8(const ModelDev* __restrict__ md, const double* __restrict__ K,
                               const double* __restrict__ Ks, const GenParams& gp, int H,
                               const float* __restrict__ x_t, const float* __restrict__ u_user,
@@ -333,8 +334,7 @@ __device__ int evaluate64_rc8(const ModelDev* __restrict__ md, const double* __r
   // Lane j's box: the limit of component j and whether it is boxed.
   const double lim_j = m->comp_lim[j];
   const bool box_j = (m->comp_mask >> j) & 1;
-  const bool noisy = md->has_noise != 0;
-  const uint64_t pre = noisy ? hash_prefix(gp.seed, gp.tick, (uint64_t)(uint32_t)gp.loop, (uint64_t)c) : 0ull;
+  const uint64_t pre = NOISE ? hash_prefix(gp.seed, gp.tick, (uint64_t)(uint32_t)gp.loop, (uint64_t)c) : 0ull;
   // Iteration s forms x_s from x_{s-1} and, beside it, the verdict of
   // x_{s-1} (the two are independent, so their chains overlap); an unsafe
   // x_{s-1} ends the rollout at s - 1 and the step formed with it is dropped.
@@ -377,7 +377,7 @@ __device__ int evaluate64_rc8(const ModelDev* __restrict__ md, const double* __r
 #pragma unroll
     for (int k = 0; k < 6; ++k) x[k] = xn[k];
     own = y;
-    if (noisy) {
+    if constexpr (NOISE) {
       add_noise64(m, pre, s, 6, x);
       own = x[0];
 #pragma unroll
@@ -460,10 +460,9 @@ __device__ __forceinline__ RcLane64<DEG> rc_lane64(const Model64* __restrict__ m
 // argument, and DPP moves hand the four values round.  Leading zero
 // coefficients leave a partial sum unchanged.  The noise draws are formed by
 // every lane; lane j tests component j's box.  Returns the first violation
-// (1..H, or H + 1).  FAR: the library's sine and cosine, for any heading; the
-// other form returns -1 when a heading leaves the reduction's range (its caller
-// then takes FAR), so that the library code's registers do not weigh on the
-// loop.
+// (1..H, or H + 1), or -1 when a heading leaves the reduction's range before
+// one (the caller then takes evaluate64_rc8), so that the registers of the
+// library's sine and cosine do not weigh on the loop.
 //
 // Bound: one wave's chain, about 770 cycles per step against about 1400 for
 // the 8-lane form (its coefficients come from LDS at every step, and its
@@ -471,7 +470,7 @@ __device__ __forceinline__ RcLane64<DEG> rc_lane64(const Model64* __restrict__ m
 // 41 us by the 8-lane form.
 // Of its step neither the column's terms, the exit nor 1 / rho shows when it is
 // taken out; the heading's series and its exchange do.
-template <int DEG, bool NOISE, bool FAR>
+template <int DEG, bool NOISE>
 __device__ __forceinline__ int evaluate64_rc16(const ModelDev* __restrict__ md, RcLane64<DEG>& ln,
                                                const GenParams& gp, int H, const float* __restrict__ x_t,
                                                const float* __restrict__ u_user, const float* __restrict__ cand,
@@ -560,18 +559,13 @@ __device__ __forceinline__ int evaluate64_rc16(const ModelDev* __restrict__ md, 
       h = fma(h, arg, ln.hc[NH - 1]);
       const double ya = fma_here(x[1], tc[1], fma_here(x[3], tc[3], mul_here(x[5], tc[5])));
       const double yb = fma_here(x[0], tc[0], fma_here(x[2], tc[2], mul_here(x[4], tc[4])));
-      double sp, cp;
-      if constexpr (FAR) {
-        sincos_rr64(x[2], &sp, &cp);
-      } else {
-        const double v = fma(z * (is_sin ? t : z), h, is_sin ? t : fma(-0.5, z, 1.0));
-        const double s0 = row_lane<0>(v), c0 = row_lane<1>(v);
-        const int q = (int)kq;  // |kq| < 2^20 where the result is used
-        const bool swap = (q & 1) != 0;
-        const double sv = swap ? c0 : s0, cv = swap ? s0 : c0;
-        sp = (q & 2) ? -sv : sv;
-        cp = ((q + 1) & 2) ? -cv : cv;
-      }
+      const double v = fma(z * (is_sin ? t : z), h, is_sin ? t : fma(-0.5, z, 1.0));
+      const double s0 = row_lane<0>(v), c0 = row_lane<1>(v);
+      const int q = (int)kq;  // |kq| < 2^20 where the result is used
+      const bool swap = (q & 1) != 0;
+      const double sv = swap ? c0 : s0, cv = swap ? s0 : c0;
+      const double sp = (q & 2) ? -sv : sv;
+      const double cp = ((q + 1) & 2) ? -cv : cv;
       double y = (fma(cp, tc[7], fma(sp, tc[6], cu)) + ya) + yb;  // rc_column64
       // Formed above the exit, where it fills the polynomials' chain.
       asm volatile("" : "+v"(y));
@@ -579,7 +573,7 @@ __device__ __forceinline__ int evaluate64_rc16(const ModelDev* __restrict__ md, 
       // is not checked.  One ballot decides the usual case, that every row goes on.
       const double P = row_lane<2>(h), Q = row_lane<3>(h);
       const bool ok = (fabs(own) < ln.lim || !ln.box) && (fabs(rho - fma(s1, Q, P)) < ln.trk_lim || !ln.track);
-      const bool near = FAR || fabs(x[2]) < 0x1p20;
+      const bool near = fabs(x[2]) < 0x1p20;
       if ((__builtin_amdgcn_ballot_w64(!(ok && near)) & live) != 0ull) {
         const bool bad = s > 1 && ((__builtin_amdgcn_ballot_w64(!ok) >> row) & 0xFFFFull) != 0ull;
         const bool ends = ((live >> row) & 1ull) != 0ull && (bad || !near);
@@ -897,10 +891,16 @@ static auto described_kernel(bool wide) {  // wide: more than 32 features
 }
 
 // Race car: four kept candidates to a wave (evaluate64_rc16), or eight
-// (evaluate64_rc8) where four would take more than two waves per SIMD.  One
-// wave per workgroup.  The 16-lane form's chain is the shorter, the 8-lane form
-// does less per candidate.  1,048,576 candidates, 60 steps: with 6,986 kept 462
-// us by 16 lanes and 466 by 8; with 12,117 kept 500 us by 16 lanes and 473 by 8.
+// (evaluate64_rc8) where four would take more than two waves per SIMD, and for
+// the candidates that the 16-lane form hands back (a heading out of its range:
+// their list entry, inverted, marks them).  One wave per workgroup.  The
+// 16-lane form's chain is the shorter, the 8-lane form does less per candidate.
+// Ticks with every candidate kept, 60 steps: 8,192 take 100 us by 16 lanes and
+// 105 by 8; 16,384 159 and 119.  One copy of each form fits two waves per SIMD
+// without scratch, which ticks that may not allocate rely on; with a second
+// 16-lane copy for far headings beside them 148 bytes a lane went to scratch,
+// the 8-lane loop read them at every step, and 65,536 kept took 325 us against
+// 309, 262,144 985 against 956.
 constexpr int kRowEntries = 8192;
 template <int DEG, bool NOISE>
 __global__ void __launch_bounds__(kR64Block, 2)
@@ -920,7 +920,7 @@ recheck64_rc_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const 
   const int per = rows ? kR64Block / 16 : kR64Block / 8;  // candidates per workgroup pass
   const int parts = min((int)gridDim.x, (n_keep + per - 1) / per);
   if ((int)blockIdx.x >= parts) return;  // uniform
-  const int* keep = rl->idx + capacity;
+  int* keep = rl->idx + capacity;
   const int lane = threadIdx.x;
   unsigned long long ks = kKeyNone, kf = kKeyNone;
   unsigned int n_safe = 0;
@@ -934,29 +934,37 @@ recheck64_rc_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const 
     kf = b < kf ? b : kf;
     n_safe += (safe && c > 0) ? 1u : 0u;
   };
+  bool far = false;
   if (rows) {
     const int j = min(lane & 15, 5), role = lane & 3;
     RcLane64<DEG> ln = rc_lane64<DEG>(&md->m64, j, role);
     for (int q0 = blockIdx.x * per; q0 < n_keep; q0 += parts * per) {  // uniform
       const int q = q0 + (lane >> 4);
       const bool valid = q < n_keep;
-      const int c = keep[valid ? q : n_keep - 1] >> 1;
-      int fv = evaluate64_rc16<DEG, NOISE, false>(md, ln, gp, H, x_t, u_user, cand, c, valid, j, role);
-      if (__builtin_amdgcn_ballot_w64(valid && fv < 0) != 0ull) {
-        const int far = evaluate64_rc16<DEG, NOISE, true>(md, ln, gp, H, x_t, u_user, cand, c, valid && fv < 0, j,
-                                                          role);
-        fv = fv < 0 ? far : fv;
+      const int entry = keep[valid ? q : n_keep - 1];
+      const int fv = evaluate64_rc16<DEG, NOISE>(md, ln, gp, H, x_t, u_user, cand, entry >> 1, valid, j, role);
+      if (valid && (lane & 15) == 0) {
+        if (fv < 0) {
+          keep[q] = ~entry;  // negative: entries are not
+          far = true;
+        } else {
+          publish(entry >> 1, fv);
+        }
       }
-      if (valid && (lane & 15) == 0) publish(c, fv);
     }
-  } else {
+  }
+  if (!rows || __builtin_amdgcn_ballot_w64(far) != 0ull) {  // uniform
     const double* Kg = &md->m64.K[0][0];
     for (int e = lane; e < MPMI_MAX_DIM * 8; e += kR64Block) sK[e] = Kg[e];
     for (int e = lane; e < kRcStepRows * 8; e += kR64Block) sKs[e] = (&md->m64.Kstep[0][0])[e];
     __syncthreads();
-    for (int q = blockIdx.x * per + (lane >> 3); q < n_keep; q += parts * per) {  // uniform per 8-lane group
-      const int c = keep[q] >> 1;
-      const int fv = evaluate64_rc8<DEG>(md, sK, sKs, gp, H, x_t, u_user, cand, c);
+    for (int q0 = blockIdx.x * per; q0 < n_keep; q0 += parts * per) {
+      const int q = q0 + (lane >> 3);  // uniform per 8-lane group, as all that follows
+      if ((lane >> 3) >= per || q >= n_keep) continue;
+      const int entry = keep[q];
+      if (rows && entry >= 0) continue;
+      const int c = (rows ? ~entry : entry) >> 1;
+      const int fv = evaluate64_rc8<DEG, NOISE>(md, sK, sKs, gp, H, x_t, u_user, cand, c);
       if ((lane & 7) == 0) publish(c, fv);
     }
   }
