@@ -826,11 +826,15 @@ __device__ __forceinline__ int evaluate64_row(const ModelDev* __restrict__ md, c
   return fv;
 }
 
-// Described bases: one kept candidate per 16-lane row, or one per lane above
-// kRowEntriesDescribed, where the lane form's waves, full, do less in all.  A
-// tick with every candidate kept, rows and lanes: balance bot, 50 steps, 64
-// candidates 49 and 219 us, 8,192: 108 and 229, 32,768: 229 and 255, 49,152: 310
-// and 277; the three-input car, 64 features, 25 steps, 32,768: 299 and 391.
+// Described bases: one kept candidate per 16-lane row, or, for bases of up to 32
+// features, one per lane above kRowEntriesDescribed, where the lane form's
+// waves, full, do less in all.  A tick with every candidate kept, rows and
+// lanes: balance bot, 50 steps, 64 candidates 49 and 219 us, 8,192: 108 and 229,
+// 32,768: 229 and 255, 49,152: 310 and 277.  With more features a row's
+// coefficients leave room for one wave per SIMD, and the lane form in the same
+// kernel has no more: three-input car, 64 features, 25 steps, 32,768: 299 and
+// 391; 49,152: 399 and 605; 262,144: 1671 and 2368 (by itself, three waves per
+// SIMD, the lane form takes 485 and 1762).
 constexpr int kRowEntriesDescribed = 32768;
 template <int DEG, int KD, bool NOISE>
 __global__ void __launch_bounds__(kR64Block)
@@ -846,7 +850,7 @@ recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const flo
   const unsigned int kn = rl->n_keep;
   const int n_keep = (int)(kn < (unsigned int)capacity ? kn : (unsigned int)capacity);
   if (recheck_nothing_kept(md, gp, H, u_user, cand, slot, out, rl, n_keep)) return;
-  const bool rows = n_keep <= kRowEntriesDescribed;
+  const bool rows = KD > 32 || n_keep <= kRowEntriesDescribed;
   const int per = rows ? kR64Block / 16 : kR64Block;  // candidates per workgroup pass
   const int parts = min((int)gridDim.x, (n_keep + per - 1) / per);
   if ((int)blockIdx.x >= parts) return;  // uniform
