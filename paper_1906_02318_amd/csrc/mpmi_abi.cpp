@@ -608,8 +608,8 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
 // Race car, H = 60, us by lanes 1 / 2 / 4 / 8: 8,192 candidates 75 / 32 / 27 /
 // 26; 10,001 75 / 32 / 28 / 30; 16,384 75 / 33 / 29.5 / 32; 20,001 75 / 34 / 36 /
 // 37; 32,768 75 / 36 / 38 / 46.  One more is a wave more than the SIMDs hold of the
-// two-lane form at its ease, and its tighter instance takes over: 32,769 75 / 40 /
-// 46 / 47; 49,152 76 / 50 / 55 / 63; 65,536 77 / 53 / 68 / 79; 65,537, a third wave,
+// two-lane form at its ease, and its tighter instance takes over: 32,769 75 / 38 /
+// 46 / 47; 49,152 76 / 46 / 55 / 63; 65,536 77 / 48 / 68 / 79; 65,537, a third wave,
 // 77 / 90 / 78 / 82.  (FP32_RECHECK64 adds its two launches to each.)
 // The balance bot's step is short and the publication of a workgroup (15 ns
 // each) weighs more than its columns: H = 50, 1,024 candidates 29 / 13.0 / 11.3 /

@@ -129,27 +129,40 @@ struct SplitFold {
 // This lane's columns of the per-step rows (quadratic state features, and for
 // the race car the six heading cross terms), held in registers for the whole
 // horizon: at one or two waves per SIMD nothing hides LDS latency, and a wave
-// of this kernel has the register file to itself.
-template <int BASIS, int J>
+// of this kernel has the register file to itself.  LAST: the last rows that an
+// instance with less room reads from LDS at every step instead; the step takes
+// them last, so the reads, issued at its start, are back by then.
+template <int BASIS, int J, int LAST = 0>
 struct SplitRows {
   static constexpr int NQ = (BASIS == MPMI_BASIS_RACE_CAR) ? 21 : 10;
   static constexpr int NT = (BASIS == MPMI_BASIS_RACE_CAR) ? 6 : 0;
-  float q[NQ][J], t[NT > 0 ? NT : 1][J];
+  static constexpr int NR = NQ + NT, HELD = NR - LAST;
+  float k[NR][J];
+  const float* last;  // LDS, row HELD
   __device__ __forceinline__ void load(const float* sK8, int D, int colpos) {
 #pragma unroll
-    for (int r = 0; r < NQ; ++r) ldsJ<J>(&sK8[(D + r) * 8 + colpos], q[r]);
+    for (int r = 0; r < HELD; ++r) ldsJ<J>(&sK8[(D + r) * 8 + colpos], k[r]);
+    last = &sK8[(D + HELD) * 8 + colpos];
+  }
+  // At the start of every step.
+  __device__ __forceinline__ void load_last() {
+    if constexpr (LAST > 0) {
+      int off = 0;
+      asm volatile("" : "+v"(off));  // or the reads would be hoisted out of the horizon loop
 #pragma unroll
-    for (int r = 0; r < NT; ++r) ldsJ<J>(&sK8[(D + NQ + r) * 8 + colpos], t[r]);
+      for (int r = 0; r < LAST; ++r) ldsJ<J>(last + off + r * 8, k[HELD + r]);
+    }
   }
 };
 
 // This lane's columns of the next state, in the one-lane kernel's operation
 // order, so the two give bit-identical states: race car as the feature sum,
 // balance bot nested.
-template <int BASIS, int J>
-__device__ __forceinline__ void split_step(const SplitFold<BASIS, J>& F, const SplitRows<BASIS, J>& Kr, const float* x,
+template <int BASIS, int J, int LAST>
+__device__ __forceinline__ void split_step(const SplitFold<BASIS, J>& F, SplitRows<BASIS, J, LAST>& Kr, const float* x,
                                            float (&y)[J]) {
   constexpr int NS = Dims<BASIS>::N;
+  Kr.load_last();
   if constexpr (BASIS == MPMI_BASIS_RACE_CAR) {
     const float sp = __sinf(x[2]), cp = __cosf(x[2]);
 #pragma unroll
@@ -166,13 +179,13 @@ __device__ __forceinline__ void split_step(const SplitFold<BASIS, J>& F, const S
       for (int l = k; l < NS; ++l, ++q) {
         const float p = x[k] * x[l];
 #pragma unroll
-        for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(p, Kr.q[q][jj], y[jj]);
+        for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(p, Kr.k[q][jj], y[jj]);
       }
     const float tp[6] = {sp * x[3], sp * x[4], sp * x[5], cp * x[3], cp * x[4], cp * x[5]};
 #pragma unroll
     for (int r = 0; r < 6; ++r)
 #pragma unroll
-      for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(tp[r], Kr.t[r][jj], y[jj]);
+      for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(tp[r], Kr.k[q + r][jj], y[jj]);
   } else {
     // y = c + sum_k x_k (L_k + sum_{l >= k} Q_kl x_l) per output column.
 #pragma unroll
@@ -186,7 +199,7 @@ __device__ __forceinline__ void split_step(const SplitFold<BASIS, J>& F, const S
 #pragma unroll
       for (int l = k; l < NS; ++l, ++q)
 #pragma unroll
-        for (int jj = 0; jj < J; ++jj) t[jj] = fmaf(Kr.q[q][jj], x[l], t[jj]);
+        for (int jj = 0; jj < J; ++jj) t[jj] = fmaf(Kr.k[q][jj], x[l], t[jj]);
 #pragma unroll
       for (int jj = 0; jj < J; ++jj) y[jj] = fmaf(x[k], t[jj], y[jj]);
     }
@@ -342,9 +355,13 @@ __device__ __forceinline__ void split_finish(const ModelDev* __restrict__ md, co
 //
 // WAVES: waves per SIMD to leave room for.  The race car's two-lane form holds
 // three columns of K and takes more than half the registers; an instance with
-// room for two waves (19 to 27 values in scratch, three loads of them a step)
-// serves ticks of more than one: 32,769 candidates 40 us against 53 in two turns,
-// 65,536 52.5 against 64; 32,768, one wave each, 40 against 34.6.
+// room for two waves serves ticks of more than one: 32,769 candidates 37.5 us
+// against 53 in two turns, 65,536 47.4 against 64; 32,768, one wave each, 40 against
+// 34.6.  It reads its last kLastRows rows from LDS at every step (SplitRows); held,
+// they put 19 to 33 values in scratch (39.6 and 51.3 us; FP32_RECHECK64, 65,536, 62.5
+// against 53.4), which ticks that may not allocate must not need.  With eight the
+// degree-8 instances still spill.
+constexpr int kLastRows = 10;
 template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED, int WAVES>
 __global__ void __launch_bounds__(256, WAVES)
 tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
@@ -378,7 +395,7 @@ tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const fl
   stage_K_split<BASIS, J>(md, sK8);
   SplitFold<BASIS, J> F;
   F.fold(sK8, colpos, u);
-  SplitRows<BASIS, J> Kr;
+  SplitRows<BASIS, J, (WAVES > 1) ? kLastRows : 0> Kr;
   Kr.load(sK8, D, colpos);
   SafetyRegs<NS, DEG, TRACK, RECHECK> sr;
   sr.load(md);
@@ -445,8 +462,8 @@ tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const fl
       F.fold(sK8, colpos, u);
     }
     float y[J];
-    split_step<BASIS, J>(F, Kr, x, y);
-  // The verdict of x_{s-1}, beside the step that forms x_s (the two chains
+    split_step(F, Kr, x, y);
+    // The verdict of x_{s-1}, beside the step that forms x_s (the two chains
     // overlap; an unsafe x_{s-1} ends the rollout and x_s is dropped).  The
     // group's lanes hold identical states (same values, same operations).
     const unsigned long long bad = failing();
@@ -508,7 +525,7 @@ rollout_split_kernel(const ModelDev* __restrict__ md, int Nc, int S, int H, cons
       F.fold(sK8, colpos, u);
     }
     float y[J];
-    split_step<BASIS, J>(F, Kr, x, y);
+    split_step(F, Kr, x, y);
     rebuild_state<NS, J, SPLIT>(y, x);
     settle_state<NS>(x);
 #pragma unroll

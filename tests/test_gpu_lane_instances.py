@@ -1,0 +1,78 @@
+"""The race car's several-lane tick kernels, one instance per number of lanes,
+track polynomial (none, degree 5, degree 8) and precision, two of the two-lane
+form: each takes the record and the first violations of the one-lane form, at
+workgroups of 64 and 256.  The instances that a learned tick's fallback runs
+take those of the same tick by itself."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_1906_02318_amd import mpmi
+from paper_1906_02318_amd.proposal import ASSET, LearnedTicker, ProposalNet
+from tests import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+PRECS = pytest.mark.parametrize("prec", [mpmi.PREC_FP32, mpmi.PREC_FP32_RECHECK64], ids=["fp32", "recheck64"])
+TRACKS = pytest.mark.parametrize("track", ["none", "degree5", "degree8"])
+
+
+def _dev(v):
+    return torch.tensor(np.asarray(v), dtype=torch.float32, device="cuda")
+
+
+def _model(ctx, kind):
+    """(model, track of the states, boxes: several on one component, or several components)"""
+    tr = synth.Track(amp=np.array([1.0, 0.5, 0.3, 0.2]), freq=np.array([3, 5, 7, 8]),
+                     phase=np.random.default_rng(11).uniform(0.0, 2 * np.pi, size=4)) if kind == "degree8" else W.rc_track()
+    boxes = {"none": [(4, 1.0, 0.0), (3, 12.0, 0.0), (5, 1.5, 0.0)], "degree5": [(4, 2.0, 0.0)],
+             "degree8": [(4, 2.0, 0.0), (4, 1.25, 0.0), (5, 0.5, 0.0)]}[kind]
+    sys = mpmi._sys(mpmi.BASIS_RACE_CAR, 6, 2, boxes, synth.RC_U_LO, synth.RC_U_HI,
+                    track=None if kind == "none" else W.track_dict(tr), eps_box=[0.02] * len(boxes), eps_track=0.02)
+    return mpmi.mpmi_model_pack(ctx, sys, torch.tensor(W.rc_model()[0], device="cuda")), tr
+
+
+# eight lanes, four, two with one wave per SIMD, two with room for two
+@PRECS
+@TRACKS
+@pytest.mark.parametrize("N", [4000, 16384, 20000, 40000])
+def test_every_instance_decides_as_the_one_lane_form(track, N, prec):
+    ctx = mpmi.Context(0)
+    model, tr = _model(ctx, track)
+    states = synth.race_car_states(2, tr, seed=4, offset=1.5, vy=(-0.3, 0.3), r=(-0.2, 0.2))
+    users = synth.uniform_user(2, synth.RC_U_LO, synth.RC_U_HI, seed=5)
+    for i in range(2):
+        x, u = _dev(states[i]), _dev(users[i])
+        got = []
+        for block in (512, 64, 256):  # 512: one lane per candidate
+            fv = torch.zeros(N + 1, dtype=torch.int16, device="cuda")
+            d = mpmi.tick_desc(N, 45, gen=mpmi.GEN_UNIFORM, n_seg=3, seed=3, tick=i, precision=prec, block=block)
+            got.append((mpmi.mpmi_tick(ctx, model, d, x, u, first_violation=fv), fv))
+        for rec, fv in got[1:]:
+            assert torch.equal(rec, got[0][0]), (mpmi.decode_selection(rec), mpmi.decode_selection(got[0][0]))
+            assert torch.equal(fv, got[0][1])
+
+
+@PRECS
+@TRACKS
+@pytest.mark.parametrize("grid", [[63, 64], [128, 128], [150, 150], [200, 200]])
+def test_a_learned_ticks_fallback_decides_as_its_tick(track, grid, prec):
+    ctx = mpmi.Context(0)
+    model, tr = _model(ctx, track)
+    ticker = LearnedTicker(ctx, model, ProposalNet.load(ctx, ASSET), proposals=1, horizon=45, fallback_grid=grid,
+                           precision=prec)
+    states, users = synth.race_car_states(12, tr, seed=6), synth.uniform_user(12, synth.RC_U_LO, synth.RC_U_HI, seed=7)
+    N = grid[0] * grid[1]
+    fell_back = 0
+    for i in range(12):
+        x, u = _dev(states[i]), _dev(users[i])
+        rec = ticker.tick(x, u, tick=i)
+        if mpmi.decode_selection(rec)["n_cand"] != N + 1:
+            continue
+        fell_back += 1
+        d = mpmi.tick_desc(N, 45, gen=mpmi.GEN_GRID, grid=grid, precision=prec, loop=2)
+        assert torch.equal(rec, mpmi.mpmi_tick(ctx, model, d, x, u))
+    assert fell_back

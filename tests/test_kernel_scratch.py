@@ -55,8 +55,8 @@ def kernels():
     return [k for elf in _code_objects(blob) for k in _kernels(elf)]
 
 
-@pytest.mark.parametrize("name", ["tick_fp32_kernel", "recheck64_filter_kernel", "recheck64_kernel",
-                                  "recheck64_rc_kernel"])
+@pytest.mark.parametrize("name", ["tick_fp32_kernel", "tick_split_kernel", "tick_custom_split_kernel",
+                                  "recheck64_filter_kernel", "recheck64_kernel", "recheck64_rc_kernel"])
 def test_the_allocation_free_ticks_kernels_need_no_scratch(kernels, name):
     mine = [k for k in kernels if f"mpmi{len(name)}{name}" in k[".name"]]
     assert mine
