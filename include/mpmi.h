@@ -672,7 +672,8 @@ mpmi_status mdn_sample(mpmi_ctx ctx, const void* model, const float* head, int32
  * lanes_per_cand as in mpmi_tick) into *out, then the exhaustive fallback
  * tick described by *fallback (GRID or UNIFORM), which runs only if *out
  * holds MPMI_NO_SAFE and then overwrites it (out->n_cand tells which
- * candidate set decided).  Each of the two ticks is FP32 or FP32_RECHECK64
+ * candidate set decided; lanes_per_cand 1 as in mpmi_tick, any other value
+ * leaves the choice to the library).  Each of the two ticks is FP32 or FP32_RECHECK64
  * (its descriptor's precision; the latter with lanes_per_cand 0 or 1 and at
  * most 2^22 candidates, and sharing the context's recheck list, so ordered
  * on one stream with the context's other such ticks).  cand_work [1][2][P]

@@ -1112,7 +1112,7 @@ mpmi_status mpmi_proposal_tick(mpmi_ctx ctx, const void* model, const uint16_t* 
   if ((pd.precision != MPMI_PREC_FP32 && !r64) || (fallback->precision != MPMI_PREC_FP32 && !fb64))
     return fail(ctx, MPMI_EUNSUPPORTED, "proposal ticks are FP32 or FP32_RECHECK64");
   if (r64 && pd.lanes_per_cand > 1)
-    return fail(ctx, MPMI_EUNSUPPORTED, "FP32_RECHECK64 proposal ticks run one lane per candidate");
+    return fail(ctx, MPMI_EUNSUPPORTED, "FP32_RECHECK64 proposal ticks: lanes_per_cand must be 0 or 1");
   if ((r64 && (long long)pd.n_cand + 1 > mpmi::kRecheckCapacity) ||
       (fb64 && (long long)fallback->n_cand + 1 > mpmi::kRecheckCapacity))
     return fail(ctx, MPMI_EUNSUPPORTED, "FP32_RECHECK64 ticks take at most %d candidates", mpmi::kRecheckCapacity);
@@ -1126,14 +1126,14 @@ mpmi_status mpmi_proposal_tick(mpmi_ctx ctx, const void* model, const uint16_t* 
                                               model, pd.n_cand, pd.seed, pd.tick, pd.loop, cand_work, st);
   void* slot = (char*)ctx->slots + (size_t)pd.loop * mpmi::slot_bytes();
   if (e == hipSuccess) {
-    e = run_tick(sys, model, pd, true, x_t, u_user, cand_work, slot, out, nullptr, nullptr, 0, ctx->recheck,
+    e = run_tick(sys, model, pd, lanes_open(sys, pd), x_t, u_user, cand_work, slot, out, nullptr, nullptr, 0, ctx->recheck,
                  mpmi::kRecheckCapacity, st);
   }
   void* slot2 = (char*)ctx->slots + (size_t)fallback->loop * mpmi::slot_bytes();
   if (e == hipSuccess) {
     mpmi_tick_desc fd = *fallback;
-    fd.lanes_per_cand = 0;
-    e = run_tick(sys, model, fd, true, x_t, u_user, nullptr, slot2, out, nullptr, nullptr, 0, ctx->recheck,
+    if (fd.lanes_per_cand > 1) fd.lanes_per_cand = 0;  // accepted, and left to the library
+    e = run_tick(sys, model, fd, lanes_open(sys, fd), x_t, u_user, nullptr, slot2, out, nullptr, nullptr, 0, ctx->recheck,
                  mpmi::kRecheckCapacity, st, out);
   }
   return check_hip(ctx, e, "mpmi_proposal_tick launch");

@@ -139,7 +139,7 @@ class LearnedTicker:
 
     def __init__(self, ctx: mpmi.Context, model: mpmi.Model, net: ProposalNet, proposals: int = 2048,
                  horizon: int = 60, fallback_grid=(128, 128), seed: int = 8, loop: int = 1, fallback_loop: int = 2,
-                 lanes_per_cand: int = 1, block: int = 0, precision: int = mpmi.PREC_FP32):
+                 lanes_per_cand: int = 0, block: int = 0, precision: int = mpmi.PREC_FP32):
         self.ctx, self.model, self.net = ctx, model, net
         self.P, self.H = proposals, horizon
         self.lanes, self.block = lanes_per_cand, block
