@@ -481,14 +481,14 @@ mpmi_status mpmi_tick_lifted(mpmi_ctx ctx, void* lifted, const mpmi_tick_desc* d
 // Lanes per candidate of an FP32 rollout that stores its states (the same bits
 // in every form), as tick_lanes, with the stores: race car, H = 60, us by lanes
 // 1 / 2 / 4 / 8: 8,192 candidates 73 / 26.5 / 21 / 18; 16,384 73 / 28 / 22 / 24;
-// 32,768 73 / 29 / 30 / 36; 32,800 73 / 49 / 35 / 40; 65,536 73 / 52 / 49 / 62;
+// 16,385 by 2 / 4 lanes 27.9 / 29.1, 16,448 26.0 / 29.0; 32,768 73 / 29 / 30 / 36; 32,800 73 / 49 / 35 / 40; 65,536 73 / 52 / 49 / 62;
 // 100,000 74 / 99 / 76 / 96.  Balance bot, H = 50: 8,192 20.5 / 10.8 / 9.5 / 9.5;
 // 32,768 21 / 11.5 / 9.5 / 18; 65,536 21 / 12.5 / 17 / 46; 131,072 22 / 25 / 32 / 101.
 static int rollout_lanes(int basis, int Nc) {
   if (basis == MPMI_BASIS_BALANCE_BOT) return Nc <= 32768 ? 4 : (Nc <= 65536 ? 2 : 1);
   if (basis != MPMI_BASIS_RACE_CAR || Nc > 65536) return 1;
   if (Nc <= 8192) return 8;
-  if (Nc <= 16384 + 64) return 4;  // 16,384 points and the user's input
+  if (Nc <= 16384) return 4;
   return Nc <= 32768 ? 2 : 4;
 }
 
@@ -606,7 +606,9 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
 // Up to 65,536 lanes are one wave per SIMD of the chip, whose step takes the
 // longer the more columns a lane forms: the most lanes that fit win, to 8.
 // Race car, H = 60, us by lanes 1 / 2 / 4 / 8: 8,192 candidates 75 / 32 / 27 /
-// 26; 10,001 75 / 32 / 28 / 30; 16,384 75 / 33 / 29.5 / 32; 20,001 75 / 34 / 36 /
+// 26; 10,001 75 / 32 / 28 / 30; 16,384 75 / 33 / 29.5 / 32; 16,385, a grid of 128 x
+// 128 and the user's input, whose one further wave ends early, by 2 / 4 lanes 32.1 /
+// 30.1; 16,391 32.0 / 34.2; 16,449 32.0 / 34.4; 20,001 75 / 34 / 36 /
 // 37; 32,768 75 / 36 / 38 / 46.  One more is a wave more than the SIMDs hold of the
 // two-lane form at its ease, and its tighter instance takes over: 32,769 75 / 38 /
 // 46 / 47; 49,152 76 / 46 / 55 / 63; 65,536 77 / 48 / 68 / 79; 65,537, a third wave,
@@ -626,7 +628,7 @@ static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj
       return c <= 8192 ? 4 : (c <= 262144 + 1 ? 2 : 1);
     case MPMI_BASIS_RACE_CAR:
       if (c <= 8192) return 8;
-      if (c <= 16384 + 64) return 4;  // 16,384 points and the user's input
+      if (c <= 16384 + 1) return 4;
       return c <= 65536 ? 2 : 1;
     case MPMI_BASIS_CUSTOM:
       return c <= 131072 + 1 ? 8 : 1;
