@@ -31,7 +31,7 @@ def _model(ctx, kind):
     boxes = {"none": [(4, 1.0, 0.0), (3, 12.0, 0.0), (5, 1.5, 0.0)], "degree5": [(4, 2.0, 0.0)],
              "degree8": [(4, 2.0, 0.0), (4, 1.25, 0.0), (5, 0.5, 0.0)]}[kind]
     sys = mpmi._sys(mpmi.BASIS_RACE_CAR, 6, 2, boxes, synth.RC_U_LO, synth.RC_U_HI,
-                    track=None if kind == "none" else W.track_dict(tr), eps_box=[0.02] * len(boxes), eps_track=0.02)
+                    track=None if kind == "none" else W.track_dict(tr), eps32_box=[0.1] * len(boxes), eps32_track=0.1)
     return mpmi.mpmi_model_pack(ctx, sys, torch.tensor(W.rc_model()[0], device="cuda")), tr
 
 
@@ -42,9 +42,10 @@ def _model(ctx, kind):
 def test_every_instance_decides_as_the_one_lane_form(track, N, prec):
     ctx = mpmi.Context(0)
     model, tr = _model(ctx, track)
-    states = synth.race_car_states(2, tr, seed=4, offset=1.5, vy=(-0.3, 0.3), r=(-0.2, 0.2))
-    users = synth.uniform_user(2, synth.RC_U_LO, synth.RC_U_HI, seed=5)
-    for i in range(2):
+    states = synth.race_car_states(4, tr, seed=4, offset=1.5, vy=(-0.3, 0.3), r=(-0.2, 0.2))
+    users = synth.uniform_user(4, synth.RC_U_LO, synth.RC_U_HI, seed=5)
+    listed = 0
+    for i in range(4):
         x, u = _dev(states[i]), _dev(users[i])
         got = []
         for block in (512, 64, 256):  # 512: one lane per candidate
@@ -54,6 +55,8 @@ def test_every_instance_decides_as_the_one_lane_form(track, N, prec):
         for rec, fv in got[1:]:
             assert torch.equal(rec, got[0][0]), (mpmi.decode_selection(rec), mpmi.decode_selection(got[0][0]))
             assert torch.equal(fv, got[0][1])
+        listed += mpmi.decode_selection(got[0][0])["n_recheck"]
+    assert (listed > 0) == (prec == mpmi.PREC_FP32_RECHECK64)
 
 
 @PRECS
