@@ -427,9 +427,10 @@ def run_trajectory_store(st: dict, reps: int = 10):
             res["separable_calls_1m"]["ms_total"] = float(sum(np.median(v) for v in ph.values()))
             res["separable_calls_1m"]["ms_fused_tick"] = times["decision"]
             res["separable_calls_1m"]["same_selection"] = bool(sel_s == sel_f)
-            # safe_mask needs, up to each first violation, the components that
-            # carry a constraint (x, y and v_y of six): those bytes, against
-            # the read ceiling of its pattern
+            # useful bytes: safe_mask needs, up to each first violation, the
+            # components that carry a constraint (x, y and v_y of six), and
+            # reads more, whole chunks until a wave's 64 candidates have ended;
+            # against the read ceiling of its pattern
             mask_gbs = units * 3 * 4 / (float(np.median(ph["safe_mask"])) * 1e-3) / 1e9
             res["separable_calls_1m"]["safe_mask_read_GB_s"] = mask_gbs
             res["separable_calls_1m"]["safe_mask_read_frac"] = mask_gbs / rceil["pattern_GB_s"]

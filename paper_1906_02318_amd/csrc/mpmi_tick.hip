@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "mpmi_device.hpp"
 #include "mpmi_launch.hpp"
@@ -89,115 +90,206 @@ rollout_fp32_kernel(const ModelDev* __restrict__ md, int Nc, int S, int H, const
   }
 }
 
-// Safety of stored trajectories (Alg. 2's check over predicted states), one
-// candidate per lane.  The states of kMaskChunk steps are loaded before any
-// of them is checked, so a lane keeps that many steps' loads in flight
-// instead of one memory round trip per step; they are then checked in step
-// order, so the first violation and the least margin up to it are those of
-// a step-by-step scan.  At most kMaskChunk - 1 steps past the first violation
-// are read and ignored.
+// Safety of stored trajectories (Alg. 2's check over predicted states): one
+// candidate per lane, P steps at a time.  All of their states are loaded before
+// the first is checked, then checked in step order, so the first violation and
+// the least margin up to it are those of a step-by-step scan.
 //
-// Bound: memory, and few waves the latency of a lane's chunks.  Of a race car's
-// six components three carry a constraint and are read: 180 of the cloud's 360
-// MB at 250,000 candidates and 60 steps, 37 us (4.9 TB/s) against 67 for all six
-// by one wave per 64 candidates; 1,000,000 139 against 258; 20,000 12 against 28.
-// Two parts take 36, 136 and 18 us, eight 41, 163 and 15.5.
-constexpr int kMaskChunk = 4;
-
-// NEAR: also the near-boundary bitmask (bit c % 32 of word c / 32 set when
-// some checked state of candidate c has a margin within its FP32 band), one
-// ballot per wave.  Blocks are whole waves; lanes past Nc take part in the
-// ballot only.
+// Bound: memory.  Only the components that carry a constraint are read (of a race
+// car's six three: 180 of the cloud's 360 MB at 250,000 candidates and 60 steps),
+// through row addresses kept in scalar registers and one 32-bit lane offset; the
+// constants of the constraints stay in registers.  With the address of every load
+// formed in vector registers and the constants fetched again at every step, some
+// 300 instructions a step, a wave took 0.4 us per step and four waves over the
+// horizon were needed to hide it, which read up to four times what an early
+// violation needs.
 //
-// A workgroup of kMaskParts waves takes 64 candidates, wave p the p-th part of
-// the horizon; the parts up to the first that holds a violation are the
-// step-by-step scan.  A wave drops the lanes that an earlier part has found
-// unsafe (what it reads of the others' finds may be old: it then scans a chunk
-// whose result is not used).
-constexpr int kMaskParts = 4;
-template <int NS, bool NEAR>
-__global__ void __launch_bounds__(64 * kMaskParts)
-mask_kernel(const ModelDev* __restrict__ md, int Nc, int H, const float* __restrict__ traj, long long traj_ld,
-            int16_t* __restrict__ fv_out, float* __restrict__ mm_out, uint32_t* __restrict__ near_bits) {
-  __shared__ volatile unsigned long long s_ended[kMaskParts];
-  __shared__ int s_fv[kMaskParts][64];
-  __shared__ float s_least[kMaskParts][64];
-  __shared__ unsigned long long s_near[kMaskParts];
-  const int lane = threadIdx.x & 63, part = threadIdx.x >> 6, c = blockIdx.x * 64 + lane;
-  const bool valid = c < Nc;
-  const int cc = valid ? c : Nc - 1;  // lanes past the end scan a valid candidate and store nothing
-  const int n = md->n;
-  const int need = (md->safe.comp_mask | (md->safe.has_track ? 3 : 0)) & ((1 << n) - 1);
-  if (threadIdx.x < kMaskParts) s_ended[threadIdx.x] = 0ull;
-  __syncthreads();
-  const int span = (H + kMaskParts * kMaskChunk - 1) / (kMaskParts * kMaskChunk) * kMaskChunk;
-  const int first = 1 + part * span, last = min(H, first + span - 1);
-  int fv = H + 1;
-  float least = INFINITY;
-  bool near = false;
-  unsigned long long going = ~0ull;
-  for (int s0 = first; s0 <= last; s0 += kMaskChunk) {
+// Advances *fv (H + 1 while safe), *least and *near (NEAR: some checked margin
+// within its FP32 band; a NaN margin is unsafe and not near) of the lanes whose
+// *fv is H + 1 over steps first .. first + P - 1, those past H dropped.  `first`
+// and `need`, the components to read, are uniform; base: the address of the
+// lane's candidate at step `first`, component 0, without its offset.
+template <int NS, bool NEAR, int P>
+__device__ __forceinline__ void mask_steps(const SafetyConsts& sc, int need, int n, const char* base, size_t row,
+                                           uint32_t off, int first, int H, int* fv, float* least, bool* near) {
+  float x[NS][P], mm[P];
+  unsigned long long nan[P], nr[P];
+  const size_t step = (size_t)n * row;
+  if (need == (1 << n) - 1) {  // every component: rows in memory order, no branch between the loads
+    const char* b = base;
 #pragma unroll
-    for (int p = 0; p < kMaskParts - 1; ++p)
-      if (p < part) going &= ~s_ended[p];
-    if (going == 0ull) break;
-    float x[kMaskChunk][NS];
-    // The components that carry a constraint, the others zero (no margin
-    // reads them).  A step past the horizon rereads the last one (never
-    // checked), so that every load of the chunk is issued before the first is
-    // waited for.
+    for (int k = 0; k < P; ++k) {
+#pragma unroll
+      for (int j = 0; j < NS; ++j) x[j][k] = *reinterpret_cast<const float*>(b + (size_t)min(j, n - 1) * row + off);
+      if (first + k < H) b += step;  // a step past the horizon rereads the last one
+    }
+  } else {
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
+      const char* b = base + (size_t)j * row;
+#pragma unroll
+      for (int k = 0; k < P; ++k) x[j][k] = 0.0f;
       if ((need >> j) & 1) {  // uniform
 #pragma unroll
-        for (int k = 0; k < kMaskChunk; ++k)
-          x[k][j] = traj[((size_t)(min(s0 + k, H) - 1) * n + j) * (size_t)traj_ld + cc];
-      } else {
-#pragma unroll
-        for (int k = 0; k < kMaskChunk; ++k) x[k][j] = 0.0f;
-      }
-    }
-    if ((going >> lane) & 1ull) {
-#pragma unroll
-      for (int k = 0; k < kMaskChunk; ++k) {
-        if (s0 + k > last) break;
-        const float mg = NEAR ? min_margin_near<NS>(md, x[k], &near) : min_margin<NS>(md, x[k]);
-        least = (mg != mg) ? mg : fminf(least, mg);
-        if (!(mg > 0.0f)) {
-          fv = s0 + k;
-          break;
+        for (int k = 0; k < P; ++k) {
+          x[j][k] = *reinterpret_cast<const float*>(b + off);
+          if (first + k < H) b += step;
         }
       }
     }
-    const unsigned long long ended = __ballot(fv <= H);
-    going &= ~ended;
-    if (lane == 0) s_ended[part] = ended;
   }
-  s_fv[part][lane] = fv;
-  s_least[part][lane] = least;
-  const unsigned long long nearest = __ballot(near);
-  if (lane == 0) s_near[part] = nearest;
-  __syncthreads();
-  if (part > 0) return;
 #pragma unroll
-  for (int p = 1; p < kMaskParts; ++p) {
-    if (fv > H) {
-      const float l = s_least[p][lane];
-      least = (l != l) ? l : fminf(least, l);
-      near |= (s_near[p] >> lane) & 1ull;
-      fv = s_fv[p][lane];
+  for (int k = 0; k < P; ++k) {
+    mm[k] = INFINITY;
+    nan[k] = nr[k] = 0ull;
+  }
+  // Uniform branches around the P steps of a constraint.
+  auto take = [&](int k, float mg, float eps) {
+    nan[k] |= __builtin_amdgcn_ballot_w64(mg != mg);
+    mm[k] = fminf(mm[k], mg);
+    if constexpr (NEAR) nr[k] |= __builtin_amdgcn_ballot_w64(fabsf(mg) < eps);
+  };
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    if (!((sc.comp_mask >> j) & 1)) continue;
+#pragma unroll
+    for (int k = 0; k < P; ++k) take(k, sc.comp_lim[j] - fabsf(x[j][k]), sc.comp_eps[j]);
+  }
+  if (sc.has_track) {
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const float xy[2] = {x[0][k], x[1][k]};
+      float rho;
+      const float rc = track_centre(&sc, xy, &rho);
+      take(k, sc.trk_lim - fabsf(rho - rc), sc.trk_eps);
     }
   }
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    if (first + k > H) break;  // uniform
+    const bool go = *fv > H, bad = (nan[k] >> lane) & 1ull;
+    *least = go ? (bad ? NAN : fminf(*least, mm[k])) : *least;
+    if constexpr (NEAR) *near |= go && ((nr[k] >> lane) & 1ull);
+    *fv = go && (bad || !(mm[k] > 0.0f)) ? first + k : *fv;
+  }
+}
+
+// The components a safety check reads.
+__device__ __forceinline__ int mask_components(const SafetyConsts& sc, int n) {
+  return (sc.comp_mask | (sc.has_track ? 3 : 0)) & ((1 << n) - 1);
+}
+
+// Results of one candidate per lane, and NEAR: the near-boundary bitmask (bit
+// c % 32 of word c / 32), one ballot per wave.
+template <bool NEAR>
+__device__ __forceinline__ void mask_store(int c, int Nc, int fv, float least, bool near, int16_t* __restrict__ fv_out,
+                                           float* __restrict__ mm_out, uint32_t* __restrict__ near_bits) {
+  const bool valid = c < Nc;
   if (valid) {
     fv_out[c] = (int16_t)fv;
     if (mm_out) mm_out[c] = least;
   }
-  if (NEAR) {
+  if constexpr (NEAR) {
     const unsigned long long b = __ballot(valid && near);
-    const int c0 = c - lane;
+    const int lane = threadIdx.x & 63, c0 = c - lane;
     if (lane == 0 && c0 < Nc) near_bits[c0 >> 5] = (uint32_t)b;
     if (lane == 32 && c0 + 32 < Nc) near_bits[(c0 >> 5) + 1] = (uint32_t)(b >> 32);
   }
+}
+
+// Large clouds: a wave goes through the horizon by itself, kMaskChunk steps at a
+// time, and stops when its 64 candidates have ended, so at most kMaskChunk - 1
+// steps past the last one's violation are read.  H = 60, us (with every component
+// by one wave and 300 instructions a step; with four waves): 250,000 candidates
+// safe 30 (67; 39), all unsafe within four steps 4.7 (6.1; 17), with every
+// component constrained 65 (70; 75) and 5.0 (6.8; 27); 1,000,000 130 (257; 144), 10.5
+// (18; 51), 256 (270; 265) and 17.5 (18; 100).  Lanes past Nc scan the last candidate
+// and store nothing.
+constexpr int kMaskChunk = 4;
+template <int NS, bool NEAR>
+__global__ void __launch_bounds__(64)
+mask_kernel(const ModelDev* __restrict__ md, int Nc, int H, const float* __restrict__ traj, long long traj_ld,
+            int16_t* __restrict__ fv_out, float* __restrict__ mm_out, uint32_t* __restrict__ near_bits) {
+  const SafetyConsts sc = md->safe;
+  const int c = blockIdx.x * 64 + threadIdx.x, n = md->n, need = mask_components(sc, n);
+  const uint32_t off = 4u * (uint32_t)min(c, Nc - 1);
+  const size_t row = 4 * (size_t)traj_ld;
+  const char* base = reinterpret_cast<const char*>(traj);
+  int fv = H + 1;
+  float least = INFINITY;
+  bool near = false;
+  for (int s = 1; s <= H && __builtin_amdgcn_ballot_w64(fv > H) != 0ull; s += kMaskChunk) {
+    mask_steps<NS, NEAR, kMaskChunk>(sc, need, n, base, row, off, s, H, &fv, &least, &near);
+    base += (size_t)(kMaskChunk * n) * row;
+  }
+  mask_store<NEAR>(c, Nc, fv, least, near, fv_out, mm_out, near_bits);
+}
+
+// Small clouds, too few waves for the memory's latency: four waves share 64
+// candidates and go through the horizon together in rounds of 1, 2, 4, 8, 8, ...
+// steps each.  Rounds grow with the steps already passed, so a cloud that is
+// unsafe early has at most about twice the steps read that it needs.  Every wave
+// keeps the candidates' state, from what all left in LDS in step order; two
+// buffers, so one barrier per round.  H = 60, us (one wave as above; four waves
+// over four parts of the horizon): 2,000 candidates safe 6.9 (13; 9.9), all unsafe
+// within four steps 3.1 (3.2; 4.5); 65,000 12.2 (18; 15) and 3.5 (3.4; 7.4); 98,304 15.2
+// (19.6; 18.7) and 3.9 (3.9; 8.9), with every component constrained 24.4 (24.2; 28.2) and
+// 4.3 (4.0; 14.4).  The line is where the cloud's waves, six to a SIMD, no longer
+// all fit: 106,000 18.2 (19.8; 20.0), with every component 27.0 (24.9; 30.4).
+constexpr int kMaskWaves = 4;
+constexpr int kMaskRoundsMax = 98304;
+template <int NS, bool NEAR>
+__global__ void __launch_bounds__(64 * kMaskWaves)
+mask_rounds_kernel(const ModelDev* __restrict__ md, int Nc, int H, const float* __restrict__ traj, long long traj_ld,
+                   int16_t* __restrict__ fv_out, float* __restrict__ mm_out, uint32_t* __restrict__ near_bits) {
+  __shared__ int s_fv[2][kMaskWaves][64];
+  __shared__ float s_least[2][kMaskWaves][64];
+  __shared__ unsigned long long s_near[2][kMaskWaves];
+  const SafetyConsts sc = md->safe;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = blockIdx.x * 64 + lane, n = md->n, need = mask_components(sc, n);
+  const uint32_t off = 4u * (uint32_t)min(c, Nc - 1);
+  const size_t row = 4 * (size_t)traj_ld;
+  int fv = H + 1, buf = 0;
+  float least = INFINITY;
+  bool near = false;
+  // Steps s .. s + 4 P - 1, P to a wave; whether a candidate goes on (the same
+  // in every wave).
+  auto round = [&](auto steps, int s) {
+    constexpr int P = decltype(steps)::value;
+    const int first = s + wave * P;
+    int f = fv;
+    float l = INFINITY;
+    bool nr = false;
+    if (first <= H)
+      mask_steps<NS, NEAR, P>(sc, need, n, reinterpret_cast<const char*>(traj) + (size_t)(first - 1) * n * row, row, off,
+                              first, H, &f, &l, &nr);
+    s_fv[buf][wave][lane] = f;
+    s_least[buf][wave][lane] = l;
+    if constexpr (NEAR) {
+      const unsigned long long b = __ballot(nr);
+      if (lane == 0) s_near[buf][wave] = b;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kMaskWaves; ++w) {
+      if (fv > H) {
+        const float v = s_least[buf][w][lane];
+        least = (v != v) ? v : fminf(least, v);
+        if constexpr (NEAR) near |= (s_near[buf][w] >> lane) & 1ull;
+        fv = s_fv[buf][w][lane];
+      }
+    }
+    buf ^= 1;
+    return __builtin_amdgcn_ballot_w64(fv > H) != 0ull;
+  };
+  using std::integral_constant;
+  bool on = round(integral_constant<int, 1>{}, 1);
+  if (on && H > 4) on = round(integral_constant<int, 2>{}, 5);
+  if (on && H > 12) on = round(integral_constant<int, 4>{}, 13);
+  for (int s = 29; on && s <= H; s += 8 * kMaskWaves) on = round(integral_constant<int, 8>{}, s);
+  if (wave == 0) mask_store<NEAR>(c, Nc, fv, least, near, fv_out, mm_out, near_bits);
 }
 
 // Selection over given first violations (Alg. 2's arg-min).  A pass of a
@@ -534,12 +626,20 @@ hipError_t launch_rollout(int basis, const void* model, int Nc, int S, int H, co
   return hipGetLastError();
 }
 
+template <int NS, bool NEAR>
+static void mask_size(hipStream_t st, const ModelDev* md, int Nc, int H, const float* traj, long long traj_ld,
+                      int16_t* fv, float* mm, uint32_t* nb) {
+  const unsigned grid = blocks_for(Nc, 64);
+  if (Nc <= kMaskRoundsMax)
+    mask_rounds_kernel<NS, NEAR><<<grid, 64 * kMaskWaves, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
+  else
+    mask_kernel<NS, NEAR><<<grid, 64, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
+}
 template <int NS>
 static void mask_dispatch(hipStream_t st, const ModelDev* md, int Nc, int H, const float* traj, long long traj_ld,
                           int16_t* fv, float* mm, uint32_t* nb) {
-  const unsigned grid = blocks_for(Nc, 64);
-  if (nb) mask_kernel<NS, true><<<grid, 64 * kMaskParts, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
-  else mask_kernel<NS, false><<<grid, 64 * kMaskParts, 0, st>>>(md, Nc, H, traj, traj_ld, fv, mm, nb);
+  if (nb) mask_size<NS, true>(st, md, Nc, H, traj, traj_ld, fv, mm, nb);
+  else mask_size<NS, false>(st, md, Nc, H, traj, traj_ld, fv, mm, nb);
 }
 
 hipError_t launch_mask(int basis, const void* model, int Nc, int H, const float* traj, long long traj_ld,
