@@ -685,8 +685,9 @@ mpmi_status mpmi_proposal_tick(mpmi_ctx ctx, const void* model, const uint16_t* 
                                const mpmi_tick_desc* fallback /* host */, float* cand_work, float* head_out,
                                mpmi_selection* out, void* work, size_t work_bytes, void* stream);
 
-/* C = op(A) op(B) on the BF16 matrix-core path (test hook): A, B BF16,
- * op transposes when ta / tb is 1, C [M][N] FP32. */
+/* C = op(A) op(B) on the BF16 matrix cores, a stand-alone product (test hook;
+ * the network's own products run in kernels of their own): A, B BF16, op
+ * transposes when ta / tb is 1, C [M][N] FP32. */
 mpmi_status mpmi_gemm_bf16(mpmi_ctx ctx, const uint16_t* A, const uint16_t* B, int32_t M, int32_t N, int32_t K,
                            int32_t ta, int32_t tb, float* C, void* stream);
 

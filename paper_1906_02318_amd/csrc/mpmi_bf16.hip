@@ -30,7 +30,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 4;            // waves per workgroup (256 threads)
 constexpr int kArow = 40;            // bf16 per LDS feature row (32 + 8 pad = 80 B)
 
-// Safety verdict of x (min_margin's rule: every checked margin positive, a
+// Safety verdict of x (step_safe's rule: every checked margin positive, a
 // NaN margin unsafe) and whether some constraint margin is within its eps of
 // zero (either side), with the track's centreline evaluated once.
 template <int DEG>

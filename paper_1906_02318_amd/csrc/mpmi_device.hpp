@@ -596,14 +596,6 @@ __device__ __forceinline__ void sincos_rr64(double x, double* sn, double* cs) {
 // ---------------------------------------------------------------------------
 // Safety margins (Sec. IV-B geometric checks, Sec. V-C-1 inflation)
 // ---------------------------------------------------------------------------
-template <int NS>
-__device__ __forceinline__ float pick(const float* x, int idx) {
-  float v = x[0];
-#pragma unroll
-  for (int k = 1; k < NS; ++k) v = (idx == k) ? x[k] : v;
-  return v;
-}
-
 // Centreline radius r_c(phi) at the polar angle of (x[0], x[1]), and rho.
 // sin(h phi + p) expands into Chebyshev polynomials of cos phi (T_h, and
 // sin phi * U_{h-1}), so r_c = P(cos phi) + sin phi * Q(cos phi) with
@@ -639,66 +631,10 @@ __device__ __forceinline__ const ConstSafety* safety_of(const ModelDev* __restri
   return (const ConstSafety*)(uintptr_t)&md->safe + off;
 }
 
-// Least margin over all constraints of state x (NaN if any margin is NaN, so
-// that "safe" = (margin > 0) rejects NaN states).
-// Boxes are taken per state component (wave-uniform branches on the mask,
-// compile-time register indices): several boxes on one component reduce to
-// the least limit, which gives the same least margin.
-template <int NS, int DEG = kMaxHarm>
-__device__ __forceinline__ float min_margin(const ModelDev* __restrict__ md, const float* x);
-
-// The same over constants the caller holds (SC: SafetyConsts in registers, or
-// the model's constant-space copy).
-template <int NS, int DEG = kMaxHarm, class SC>
-__device__ __forceinline__ float min_margin_of(const SC* sc, const float* x) {
-  float mm = INFINITY;
-  bool nan = false;
-  const int mask = sc->comp_mask;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    if (mask & (1 << k)) {
-      const float mg = sc->comp_lim[k] - fabsf(x[k]);
-      nan |= (mg != mg);
-      mm = fminf(mm, mg);
-    }
-  }
-  if (sc->has_track) {
-    float rho;
-    const float rc = track_centre<DEG>(sc, x, &rho);
-    const float mg = sc->trk_lim - fabsf(rho - rc);
-    nan |= (mg != mg);
-    mm = fminf(mm, mg);
-  }
-  return nan ? NAN : mm;
-}
-
-template <int NS, int DEG>
-__device__ __forceinline__ float min_margin(const ModelDev* __restrict__ md, const float* x) {
-  return min_margin_of<NS, DEG>(safety_of(md), x);
-}
-
-// The verdict alone: min_margin(x) > 0, i.e. every margin positive.  A NaN
-// margin fails its comparison, so no NaN bookkeeping and no minimum are
-// needed; the tests combine bitwise (each a compare into a lane mask, no
-// branch, no short circuit).  Used by the lifted tick; in the FP32 tick's
-// step loop, where one component of six carries a box, uniform branches past
-// the others measured faster (step_safe).
-template <int NS, int DEG = kMaxHarm, class SC>
-__device__ __forceinline__ bool all_safe_of(const SC* sc, const float* x) {
-  bool ok = true;
-  const int mask = sc->comp_mask;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) ok &= !((mask >> k) & 1) | (sc->comp_lim[k] - fabsf(x[k]) > 0.0f);
-  if (sc->has_track) {
-    float rho;
-    const float rc = track_centre<DEG>(sc, x, &rho);
-    ok &= sc->trk_lim - fabsf(rho - rc) > 0.0f;
-  }
-  return ok;
-}
-
-// The verdict min_margin(x) > 0 of one step of a rollout, boxes by uniform
-// branches; NEAR also ORs into *near whether some margin lies within its
+// The verdict of one step of a rollout, the least margin over all constraints
+// positive and none NaN.  Boxes are taken per state component (uniform branches
+// on the mask, compile-time register indices; several boxes on one component
+// reduce to the least limit); NEAR also ORs into *near whether some margin lies within its
 // constraint's FP32 band (a NaN margin is unsafe and not near).  Comparisons
 // alone: the least margin and its NaN flag cost the race car's step, 277 vector
 // instructions, 10 more (64 loops 192 against 189 us).
@@ -724,36 +660,6 @@ __device__ __forceinline__ bool step_safe(const ModelDev* __restrict__ md, const
   }
   if constexpr (NEAR) *near |= nr;
   return ok;
-}
-
-// min_margin, also OR-ing into *near whether some constraint's margin lies
-// within that constraint's FP32 band of zero (either side; a NaN margin is
-// unsafe and not near).
-template <int NS, int DEG = kMaxHarm>
-__device__ __forceinline__ float min_margin_near(const ModelDev* __restrict__ md, const float* x, bool* near) {
-  const ConstSafety* sc = safety_of(md);
-  float mm = INFINITY;
-  bool nan = false, nr = false;
-  const int mask = sc->comp_mask;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    if (mask & (1 << k)) {
-      const float mg = sc->comp_lim[k] - fabsf(x[k]);
-      nan |= (mg != mg);
-      mm = fminf(mm, mg);
-      nr |= fabsf(mg) < sc->comp_eps[k];
-    }
-  }
-  if (sc->has_track) {
-    float rho;
-    const float rc = track_centre<DEG>(sc, x, &rho);
-    const float mg = sc->trk_lim - fabsf(rho - rc);
-    nan |= (mg != mg);
-    mm = fminf(mm, mg);
-    nr |= fabsf(mg) < sc->trk_eps;
-  }
-  *near |= nr;
-  return nan ? NAN : mm;
 }
 
 // ---------------------------------------------------------------------------

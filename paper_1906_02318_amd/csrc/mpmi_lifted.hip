@@ -316,8 +316,8 @@ lifted_tick_kernel(const LiftedDev* __restrict__ ld, GenParams gp, int H, int hp
             acc1[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[G - 1][i], B[ct][i], acc1[ct], 0, 0, 0);
         }
       };
-      // Lanes whose state of each tile is outside the safe set: min_margin > 0
-      // by a comparison into a lane mask each, the constraints by uniform
+      // Lanes whose state of each tile is outside the safe set: step_safe's
+      // verdict by a comparison into a lane mask each, the constraints by uniform
       // branches around the tiles.
       unsigned long long u[4] = {0, 0, 0, 0};
       auto outside = [&](auto live) {

@@ -41,15 +41,12 @@ struct GemmArgs {
   int M, N, K;
   int lda, ldb;
   int ta, tb;          // A(m,k) = ta ? A[k*lda+m] : A[m*lda+k]; B(k,n) = tb ? B[n*ldb+k] : B[k*ldb+n]
-  float* out_f32;      // [M][N] (single part)
-  // Split-K: gridDim.z parts of ksplit rows of K each write FP32 partial
-  // products to part[z][M][N].
-  int ksplit;
-  float* part;
+  float* out;          // [M][N]
   bool vec_a, vec_b;   // 16-byte loads allowed (leading dimension a multiple of 8, 16-byte aligned base)
 };
 
-// C = op(A) op(B) on v_mfma_f32_16x16x32_bf16.  A 256-thread workgroup owns a
+// C = op(A) op(B) on v_mfma_f32_16x16x32_bf16, a stand-alone product (the
+// network's run in mlp_fused_kernel and mlp_dw_kernel).  A 256-thread workgroup owns a
 // 64 x 64 tile of C, each wave a 32 x 32 quarter as 2 x 2 MFMA blocks.  Per
 // 32-wide k step every thread moves one 16-byte chunk (8 BF16) of A and one
 // of B from global memory into LDS, in the operand order the MFMA reads (row
@@ -139,16 +136,12 @@ __device__ __forceinline__ void gemm_store(const GemmArgs& g, const GemmChunk& c
 // after a barrier that ends the current stage's reads.
 constexpr int kGemmSub = 4;
 
-// One 64 x 64 output tile (bx, by) of K part bz; every thread of the
-// workgroup calls it.
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int bz) {
+__global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) uint16_t As[kGemmSub][64][kGemmKP];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[kGemmSub][64][kGemmKP];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = by * 64, n0 = bx * 64;
-  const int kbeg = bz * g.ksplit;
-  const int kend = min(g.K, kbeg + g.ksplit);
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64, kend = g.K;
   constexpr int kStage = 32 * kGemmSub;
   f32x4_t acc[2][2];
 #pragma unroll
@@ -157,11 +150,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   GemmChunk c[kGemmSub];
 #pragma unroll
-  for (int q = 0; q < kGemmSub; ++q) gemm_load(g, m0, n0, kbeg + 32 * q, kend, &c[q]);
+  for (int q = 0; q < kGemmSub; ++q) gemm_load(g, m0, n0, 32 * q, kend, &c[q]);
 #pragma unroll
   for (int q = 0; q < kGemmSub; ++q) gemm_store(g, c[q], As[q], Bs[q]);
   __syncthreads();
-  for (int k0 = kbeg; k0 < kend; k0 += kStage) {
+  for (int k0 = 0; k0 < kend; k0 += kStage) {
     const bool more = k0 + kStage < kend;
     if (more) {
 #pragma unroll
@@ -191,7 +184,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
     }
   }
   // D fragment: lane holds column (lane & 15), rows (lane >> 4) * 4 + r.
-  float* dst = g.part ? g.part + (size_t)bz * g.M * g.N : g.out_f32;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -200,30 +192,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int bx, int by, int
       const int n = n0 + wn * 32 + j * 16 + (lane & 15);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (mb + r < g.M && n < g.N) dst[(size_t)(mb + r) * g.N + n] = acc[i][j][r];
+        if (mb + r < g.M && n < g.N) g.out[(size_t)(mb + r) * g.N + n] = acc[i][j][r];
     }
-}
-
-__global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g) { gemm_tile(g, blockIdx.x, blockIdx.y, blockIdx.z); }
-
-// Sets a product's derived fields (16-byte load flags, K part size for
-// `splits` parts rounded to 32-row steps) and returns the number of parts.
-static int gemm_prepare(GemmArgs& g, int splits) {
-  g.vec_a = g.lda % 8 == 0 && ((uintptr_t)g.A & 15) == 0;
-  g.vec_b = g.ldb % 8 == 0 && ((uintptr_t)g.B & 15) == 0;
-  if (splits < 1) splits = 1;
-  g.ksplit = (((g.K + splits - 1) / splits) + 31) / 32 * 32;
-  return (g.K + g.ksplit - 1) / g.ksplit;
-}
-
-// Launches op(A) op(B) in `splits` parts of the K range (rounded to 32-row
-// steps; *parts_out receives the number of parts launched).
-static hipError_t gemm(GemmArgs g, hipStream_t st, int splits = 1, int* parts_out = nullptr) {
-  splits = gemm_prepare(g, splits);
-  if (parts_out) *parts_out = splits;
-  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, splits);
-  gemm_bf16_kernel<<<grid, 256, 0, st>>>(g);
-  return hipGetLastError();
 }
 
 // Max and sum over a 16-lane group (one sample's mixture components), the
@@ -1309,8 +1279,11 @@ hipError_t launch_gemm_test(const uint16_t* A, const uint16_t* B, int M, int N, 
   g.A = A; g.B = B; g.M = M; g.N = N; g.K = K; g.ta = ta; g.tb = tb;
   g.lda = ta ? M : K;
   g.ldb = tb ? K : N;
-  g.out_f32 = C;
-  return gemm(g, st);
+  g.out = C;
+  g.vec_a = g.lda % 8 == 0 && ((uintptr_t)A & 15) == 0;
+  g.vec_b = g.ldb % 8 == 0 && ((uintptr_t)B & 15) == 0;
+  gemm_bf16_kernel<<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, st>>>(g);
+  return hipGetLastError();
 }
 
 }  // namespace mpmi

@@ -207,17 +207,18 @@ __device__ __forceinline__ void split_step(const SplitFold<BASIS, J>& F, SplitRo
 }
 
 // The constraint constants in registers, loaded once per launch, and the
-// safety verdict of a state.  safe(x) equals min_margin(x) > 0: every margin
-// lim - |v| is positive and none is NaN exactly when |v| < lim holds for each
-// (with denormals kept, the difference of two distinct finite floats is never
-// rounded to zero, and a NaN fails either comparison).  The track's
+// track's verdict of a state (the boxes are tested by the lane that holds the
+// component).  A verdict is step_safe's: every margin lim - |v| is positive and
+// none is NaN exactly when |v| < lim holds for each (with denormals kept, the
+// difference of two distinct finite floats is never rounded to zero, and a NaN
+// fails either comparison).  The track's
 // centreline radius takes track_centre's operations in its order.  TRACK is
 // the model's has_track flag, fixed per kernel instance; the float constants
 // are pinned to vector registers (the scalar file is too small to hold them
 // beside the loop's own state).
 //
-// NEAR (FP32_RECHECK64): check() also ORs into *near whether some margin lies
-// within its constraint's FP32 band, as min_margin_near does.
+// NEAR (FP32_RECHECK64): track() also ORs into *near whether its margin lies
+// within the track's FP32 band.
 template <int NS, int DEG, bool TRACK, bool NEAR = false>
 struct SafetyRegs {
   float lim[NS], p[DEG + 1], q[DEG], trk_lim;
@@ -275,16 +276,6 @@ struct SafetyRegs {
     const float off = fabsf(rho - fmaf(s1, Q, P));
     if constexpr (NEAR) *near |= fabsf(trk_lim - off) < trk_eps;
     return off < trk_lim;
-  }
-  __device__ __forceinline__ bool safe(const float* x, bool* near) const {
-    bool ok = true;
-#pragma unroll
-    for (int k = 0; k < NS; ++k) ok &= (fabsf(x[k]) < lim[k]) | !chk[k];
-    if constexpr (NEAR)
-#pragma unroll
-      for (int k = 0; k < NS; ++k) *near |= fabsf(lim[k] - fabsf(x[k])) < eps[k];
-    if constexpr (TRACK) ok &= track(x[0], x[1], near);
-    return ok;
   }
 };
 
