@@ -580,7 +580,7 @@ def run_mlp_training(batch: int = 4096, steps: int = 50, warmup: int = 5):
     return {"batch": batch, "step_ms_p50": step_ms, "step_ms_wall": wall * 1e3 / steps,
             "tflops": tflops, "bf16_mfma_peak_tflops": PEAK_BF16_MFMA_TFLOPS,
             "mfma_frac": tflops / PEAK_BF16_MFMA_TFLOPS,
-            "note": (f"11 dense products of at most {batch} x 256 x 256 plus loss, split-K reductions and "
+            "note": (f"11 dense products of at most {batch} x 256 x 256 plus loss, the sums of the weight gradients' parts and "
                      "Adam; " + ("launch- and latency-bound" if batch <= 8192 else
                                  "bound by weight and activation reads and the weight-gradient operands") + "; kernel times in profiles/")}
 

@@ -974,9 +974,12 @@ __global__ void __launch_bounds__(256) mlp_reduce_kernel(ReduceGroup rg) {
 // Forward pass of the one row [x_t; u_user] in a workgroup of 1,024
 // threads, then draws from its head: each of the launch's workgroups runs the
 // same forward (bit-identical; workgroup 0 stores the head) and draws its
-// share of the P proposals, kRowDraws per workgroup and pass.  The arithmetic rules are the
-// batched path's (standardised input and activations rounded to BF16, BF16
-// weights, FP32 accumulation, FP32 bias added last).  In a layer of DIN
+// share of the P proposals, kRowDraws per workgroup and pass.  Roundings are the
+// batched path's (standardised input and activations to BF16, BF16 weights, FP32
+// accumulation and biases), but not every FP32 operation: here the bias is added
+// last, not first, and GELU takes tanhf, not the hardware exponential and
+// reciprocal, so an activation that lies at a BF16 rounding boundary can round
+// the other way in the two.  In a layer of DIN
 // inputs and DOUT units, thread t takes units [8g, 8g + 8) (g = t % (DOUT/8))
 // over inputs [8s, 8s + 8) (s = t / (DOUT/8)): eight 16-byte weight loads and
 // 64 FMAs; its eight partial sums go to LDS, where one thread per unit adds

@@ -22,7 +22,8 @@
 // candidate over sixteen lanes (one output component each, the step's
 // coefficients in registers), or eight when many are kept; the described bases
 // spread one over sixteen (an atom or two, four features and an output
-// component each), or run one per lane when very many are kept.  The many-loop
+// component each), or, of up to 32 features, run one per lane when very many are
+// kept.  The many-loop
 // form lists (loop, candidate, model) entries and prunes by each loop's K*
 // itself.
 #include <hip/hip_runtime.h>
