@@ -616,9 +616,19 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
 // The balance bot's step is short and the publication of a workgroup (15 ns
 // each) weighs more than its columns: H = 50, 1,024 candidates 29 / 13.0 / 11.3 /
 // 11.9; 8,192 29.5 / 13.5 / 12.8 / 15.8; 16,384 29.5 / 14.7 / 15.1 / 19.5; 262,145
-// 44 / 43 / 71 / 133.  A custom basis has one split form, of eight lanes
-// (three-input car, H = 25: 10,121 candidates 159 / 28.6; 60,001 162 / 80; 120,001
-// 174 / 136; level near 155,000).
+// 44 / 43 / 71 / 133.  A custom basis has one split form, of eight lanes, whose step
+// hardly depends on the number of features; the one-lane step is as long as they
+// are many, and ends with its own candidates.  By 1 / 8 lanes, three-input car, 64
+// features, H = 25: 10,121 candidates 159 / 28.6; 65,001 162 / 84; 100,001 173 / 120;
+// 131,072 174 / 147; level near 155,000.  Fewer features, H = 40, all safe: 48
+// features 65,001 219 / 113, 100,001 233 / 170, 131,072 234 / 209; 10 features 142 /
+// 98, 150 / 143, 153 / 175.  Half of the steps taken, 48 features: 110 / 79, 117 / 110,
+// 119 / 139; the balance bot's 21 features, H = 50: 141 / 122, 150 / 180, 151 / 219.
+// (131,073 was the limit for every basis.)
+//
+// A cloud that ends in its first step costs little but the publication of its
+// workgroups, of which several lanes make more: race car, 65,536, 12.4 us by one
+// lane and 18 by two; three-input car, 65,001 17 and 50 by eight, 131,072 21 and 92.
 static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj, bool open) {
   if (d.lanes_per_cand > 1) return d.lanes_per_cand;
   if (!open || traj || d.block > 256 || mpmi::system_noisy(sys)) return 1;
@@ -631,7 +641,7 @@ static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj
       if (c <= 16384 + 1) return 4;
       return c <= 65536 ? 2 : 1;
     case MPMI_BASIS_CUSTOM:
-      return c <= 131072 + 1 ? 8 : 1;
+      return c <= (sys.dim > 48 ? 131072 : 65536) + 1 ? 8 : 1;
     default:
       return 1;
   }
