@@ -613,10 +613,13 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
 // two-lane form at its ease, and its tighter instance takes over: 32,769 75 / 38 /
 // 46 / 47; 49,152 76 / 46 / 55 / 63; 65,536 77 / 48 / 68 / 79; 65,537, a third wave,
 // 77 / 90 / 78 / 82.  (FP32_RECHECK64 adds its two launches to each.)
-// The balance bot's step is short and the publication of a workgroup (15 ns
+// The balance bot's step is short and the publication of a workgroup (19 ns
 // each) weighs more than its columns: H = 50, 1,024 candidates 29 / 13.0 / 11.3 /
-// 11.9; 8,192 29.5 / 13.5 / 12.8 / 15.8; 16,384 29.5 / 14.7 / 15.1 / 19.5; 262,145
-// 44 / 43 / 71 / 133.  A custom basis has one split form, of eight lanes, whose step
+// 11.9; 8,192 29.5 / 13.5 / 12.8 / 15.8; 16,384 29.5 / 14.7 / 15.1 / 19.5; above
+// 32,768 two lanes go in workgroups of 512 where the size is left open: 65,536 33 /
+// 18.6, 131,072 37 / 23, 262,144 46 / 36, H = 10 15 / 11.7, 18.6 / 17.2, 28 / 27.  With
+// workgroups of 256 asked for: 65,536 33 / 21, 131,072 37 / 30, 262,144 46 / 46, H = 10
+// 15 / 15, 18.5 / 23.5, 28 / 40.  A custom basis has one split form, of eight lanes, whose step
 // hardly depends on the number of features; the one-lane step is as long as they
 // are many, and ends with its own candidates.  By 1 / 8 lanes, three-input car, 64
 // features, H = 25: 10,121 candidates 159 / 28.6; 65,001 162 / 84; 100,001 173 / 120;
@@ -635,7 +638,7 @@ static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj
   const long long c = (long long)d.n_cand + 1;
   switch (sys.basis) {
     case MPMI_BASIS_BALANCE_BOT:
-      return c <= 8192 ? 4 : (c <= 262144 + 1 ? 2 : 1);
+      return c <= 8192 ? 4 : (c <= (d.block == 0 ? 262144 : 65536) + 1 ? 2 : 1);
     case MPMI_BASIS_RACE_CAR:
       if (c <= 8192) return 8;
       if (c <= 16384 + 1) return 4;

@@ -354,7 +354,7 @@ __device__ __forceinline__ void split_finish(const ModelDev* __restrict__ md, co
 // degree-8 instances still spill.
 constexpr int kLastRows = 10;
 template <int BASIS, int SPLIT, int DEG, bool TRACK, bool RECHECK, bool GATED, int WAVES>
-__global__ void __launch_bounds__(256, WAVES)
+__global__ void __launch_bounds__(SPLIT == 2 && BASIS != MPMI_BASIS_RACE_CAR ? 512 : 256, WAVES)
 tick_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
                   const float* __restrict__ u_user, const float* __restrict__ cand, Slot* __restrict__ slot,
                   mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out, RecheckList* __restrict__ rl,
@@ -738,6 +738,7 @@ tick_custom_split_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, c
 struct SplitLaunch {
   unsigned grid;
   int block, split;
+  bool open_block;  // the descriptor leaves the workgroup's size to the library
   hipStream_t st;
   const ModelDev* md;
   GenParams gp;
@@ -757,9 +758,19 @@ static void split_launch(const SplitLaunch& a) {
 }
 template <int BASIS, int DEG, bool TRACK, bool RECHECK, bool GATED>
 static void split_lanes(const SplitLaunch& a) {
-  if constexpr (BASIS == MPMI_BASIS_RACE_CAR) {
-    if (a.split == 2 && (long long)a.grid * a.block > 64ll * 4 * device_cu_count())
-      return split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED, 2>(a);
+  if (a.split == 2 && (long long)a.grid * a.block > 64ll * 4 * device_cu_count()) {
+    if constexpr (BASIS == MPMI_BASIS_RACE_CAR) return split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED, 2>(a);
+    // More than a wave per SIMD, and a short step: as many candidates to a
+    // workgroup, and so as few publications (19 ns each), as in the one-lane form.
+    // Balance bot, H = 50, workgroups of 512 against 256: 65,536 candidates 18.6
+    // and 21.1 us, 262,144 36 and 46; all ending in the first step, 10.4 and 13.9, 24 and
+    // 38 (one lane 10.4 and 23).  The race car's own 65,536 take 51 and 48.
+    if (a.open_block) {
+      SplitLaunch w = a;
+      w.block = 512;
+      w.grid = (a.grid + 1) / 2;
+      return split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED>(w);
+    }
   }
   if (a.split == 2) split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED>(a);
   else if (a.split == 4) split_launch<BASIS, 4, DEG, TRACK, RECHECK, GATED>(a);
@@ -805,6 +816,7 @@ hipError_t launch_tick_split(const mpmi_system& sys, int split, const void* mode
   a.gp.n_seg = d.n_seg;
   for (int j = 0; j < MPMI_MAX_INPUT; ++j) a.gp.grid[j] = d.grid[j] > 0 ? d.grid[j] : 1;
   a.block = d.block > 0 ? d.block : 256;
+  a.open_block = d.block == 0;
   a.split = split;
   a.grid = (unsigned)((((long long)d.n_cand + 1) * split + a.block - 1) / a.block);
   a.st = st;

@@ -56,3 +56,25 @@ def test_described_bases(D, count, lanes, prec):
     assert _launches(call)[0] == ((count * lanes + 255) // 256, 256)
     one, fv1, _ = _tick(ctx, model, x, u, count - 1, prec, one_lane=True)
     assert torch.equal(out, one) and torch.equal(fv, fv1)
+
+
+# workgroups of 512 above 32,768 candidates, of the size asked for where one is; a ragged last one
+@PRECS
+@pytest.mark.parametrize("track", [False, True])
+@pytest.mark.parametrize("block,count,lanes,threads", [
+    (0, 32768, 2, 256), (0, 32769, 2, 512), (0, 33025, 2, 512), (0, 70001, 2, 512), (0, 262145, 2, 512),
+    (0, 262146, 1, 256), (256, 65537, 2, 256), (256, 65538, 1, 256), (64, 65537, 2, 64), (64, 65538, 1, 64)])
+def test_balance_bot(track, block, count, lanes, threads, prec):
+    ctx = mpmi.Context(0)
+    sys = mpmi.balance_bot_system(p_bound=0.5)
+    if track:
+        sys = mpmi._sys(mpmi.BASIS_BALANCE_BOT, 4, 1, [(2, 0.5, 0.0)], [-5.0], [5.0],
+                        track=dict(r0=0.5, half=0.4, amp=[0.1, 0.05], freq=[3, 8], phase=[0.3, 1.0], infl=0.0),
+                        eps32_box=[1e-4], eps32_track=1e-3)
+    model = mpmi.mpmi_model_pack(ctx, sys, torch.tensor(W.bb_model()[0], device="cuda"))
+    x, u = _dev([0.3, 0.2, 0.05, 0.3]), _dev([1.0])
+    out, fv, call = _tick(ctx, model, x, u, count - 1, prec, block=block, H=40)
+    assert _launches(call)[0] == ((count * lanes + threads - 1) // threads, threads)
+    one, fv1, _ = _tick(ctx, model, x, u, count - 1, prec, H=40, one_lane=True)
+    assert torch.equal(out, one) and torch.equal(fv, fv1)
+    assert int((fv == 41).sum()) not in (0, count)  # verdicts on both sides
