@@ -613,32 +613,34 @@ static mpmi_status validate_desc(mpmi_ctx ctx, const mpmi_system& sys, const mpm
 // two-lane form at its ease, and its tighter instance takes over: 32,769 75 / 38 /
 // 46 / 47; 49,152 76 / 46 / 55 / 63; 65,536 77 / 48 / 68 / 79; 65,537, a third wave,
 // 77 / 90 / 78 / 82.  (FP32_RECHECK64 adds its two launches to each.)
-// The balance bot's step is short and the publication of a workgroup (19 ns
-// each) weighs more than its columns: H = 50, 1,024 candidates 29 / 13.0 / 11.3 /
-// 11.9; 8,192 29.5 / 13.5 / 12.8 / 15.8; 16,384 29.5 / 14.7 / 15.1 / 19.5; above
-// 32,768 two lanes go in workgroups of 512 where the size is left open: 65,536 33 /
-// 18.6, 131,072 37 / 23, 262,144 46 / 36, H = 10 15 / 11.7, 18.6 / 17.2, 28 / 27.  With
-// workgroups of 256 asked for: 65,536 33 / 21, 131,072 37 / 30, 262,144 46 / 46, H = 10
-// 15 / 15, 18.5 / 23.5, 28 / 40.  A custom basis has one split form, of eight lanes, whose step
-// hardly depends on the number of features; the one-lane step is as long as they
-// are many, and ends with its own candidates.  By 1 / 8 lanes, three-input car, 64
-// features, H = 25: 10,121 candidates 159 / 28.6; 65,001 162 / 84; 100,001 173 / 120;
-// 131,072 174 / 147; level near 155,000.  Fewer features, H = 40, all safe: 48
-// features 65,001 219 / 113, 100,001 233 / 170, 131,072 234 / 209; 10 features 142 /
-// 98, 150 / 143, 153 / 175.  Half of the steps taken, 48 features: 110 / 79, 117 / 110,
-// 119 / 139; the balance bot's 21 features, H = 50: 141 / 122, 150 / 180, 151 / 219.
+// The balance bot's step is short and the publication of a workgroup (10 to 13 ns
+// each) weighs more than its columns: H = 50, 1,024 candidates 30 / 13.2 / 11.5 /
+// 11.9; 8,192 31 / 13.6 / 12.8 / 15.8; 16,384 30 / 14.7 / 13.9 / 19.5; above 32,768 two
+// lanes go in workgroups of 512 where the size is left open: 65,536 31 / 17.3, 131,072
+// 33 / 21.7, 262,144 40 / 33, H = 10 13.3 / 10.4, 15.3 / 14.2, 21 / 21.  Of 256: 131,072 34 /
+// 24, 200,001 39 / 30, H = 10 15.2 / 16.8, 18.9 / 22; of 128: 65,536 33 / 23, 131,072 37 /
+// 34, H = 10 19.5 / 25.7, and smaller ones leave two lanes at 65,537.
+// A custom basis has one split form, of eight lanes, whose step hardly depends on the
+// number of features; the one-lane step is as long as they are many, and ends with
+// its own candidates.  By 1 / 8 lanes, three-input car, 64 features, H = 25: 10,121
+// candidates 159 / 28.6; 65,001 162 / 84; 100,001 173 / 120; 131,072 174 / 147; level
+// near 155,000.  Fewer features, H = 40, all safe: 48 features 65,001 219 / 113,
+// 100,001 233 / 170, 131,072 234 / 209; 10 features 142 / 98, 150 / 143, 153 / 175.
+// Half of the steps taken, 48 features: 110 / 79, 117 / 110, 119 / 139; the balance
+// bot's 21 features, H = 50: 141 / 122, 150 / 180, 151 / 219.
 // (131,073 was the limit for every basis.)
 //
 // A cloud that ends in its first step costs little but the publication of its
-// workgroups, of which several lanes make more: race car, 65,536, 12.4 us by one
-// lane and 18 by two; three-input car, 65,001 17 and 50 by eight, 131,072 21 and 92.
+// workgroups, of which several lanes make more: race car, 8,192 8.6 us by one lane
+// and 10.6 by eight, 65,536 11.0 and 14.7 by two; three-input car by eight 10,121
+// 12.1, 65,001 36 and 131,072 66 (by one 13.5, 17 and 21).
 static int tick_lanes(const mpmi_system& sys, const mpmi_tick_desc& d, bool traj, bool open) {
   if (d.lanes_per_cand > 1) return d.lanes_per_cand;
   if (!open || traj || d.block > 256 || mpmi::system_noisy(sys)) return 1;
   const long long c = (long long)d.n_cand + 1;
   switch (sys.basis) {
     case MPMI_BASIS_BALANCE_BOT:
-      return c <= 8192 ? 4 : (c <= (d.block == 0 ? 262144 : 65536) + 1 ? 2 : 1);
+      return c <= 8192 ? 4 : (c <= (d.block % 256 == 0 ? 262144 : 65536) + 1 ? 2 : 1);
     case MPMI_BASIS_RACE_CAR:
       if (c <= 8192) return 8;
       if (c <= 16384 + 1) return 4;

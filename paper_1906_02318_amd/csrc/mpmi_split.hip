@@ -761,10 +761,10 @@ static void split_lanes(const SplitLaunch& a) {
   if (a.split == 2 && (long long)a.grid * a.block > 64ll * 4 * device_cu_count()) {
     if constexpr (BASIS == MPMI_BASIS_RACE_CAR) return split_launch<BASIS, 2, DEG, TRACK, RECHECK, GATED, 2>(a);
     // More than a wave per SIMD, and a short step: as many candidates to a
-    // workgroup, and so as few publications (19 ns each), as in the one-lane form.
-    // Balance bot, H = 50, workgroups of 512 against 256: 65,536 candidates 18.6
-    // and 21.1 us, 262,144 36 and 46; all ending in the first step, 10.4 and 13.9, 24 and
-    // 38 (one lane 10.4 and 23).  The race car's own 65,536 take 51 and 48.
+    // workgroup, and so as few publications, as in the one-lane form.  Balance bot,
+    // H = 50, workgroups of 512 against 256: 65,536 candidates 17.3 and 18.9 us, 131,072
+    // 21.7 and 24; all ending in the first step, 9.1 and 10.8, 12.2 and 15.4 (one lane 9.1
+    // and 10.9).  The race car's own 65,536 took 51 and 48.
     if (a.open_block) {
       SplitLaunch w = a;
       w.block = 512;

@@ -63,7 +63,7 @@ def test_described_bases(D, count, lanes, prec):
 @pytest.mark.parametrize("track", [False, True])
 @pytest.mark.parametrize("block,count,lanes,threads", [
     (0, 32768, 2, 256), (0, 32769, 2, 512), (0, 33025, 2, 512), (0, 70001, 2, 512), (0, 262145, 2, 512),
-    (0, 262146, 1, 256), (256, 65537, 2, 256), (256, 65538, 1, 256), (64, 65537, 2, 64), (64, 65538, 1, 64)])
+    (0, 262146, 1, 256), (256, 70001, 2, 256), (256, 262145, 2, 256), (256, 262146, 1, 256), (64, 65537, 2, 64), (64, 65538, 1, 64)])
 def test_balance_bot(track, block, count, lanes, threads, prec):
     ctx = mpmi.Context(0)
     sys = mpmi.balance_bot_system(p_bound=0.5)
