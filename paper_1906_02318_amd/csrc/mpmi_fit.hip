@@ -98,7 +98,7 @@ __device__ __forceinline__ void lift_row(const mpmi_system& sys, const double* _
 }
 
 // Accumulation on v_mfma_f64_16x16x4f64.  A tile of 64 rows of Z = [Psi | RHS]
-// sits in LDS as 16-column blocks (Psi padded with zero columns to four
+// sits in LDS as 16-column blocks (Psi padded with zero columns to PB
 // blocks, the right-hand sides to RB); an MFMA k-step takes four rows, and its
 // A and B operands are the same read of a column block (lane l: row l / 16,
 // column l % 16).  On gfx950 the instruction is a chain of four FMAs in k order
@@ -129,22 +129,27 @@ __device__ __forceinline__ double gram_frag(const double (*Z)[STRIDE], int ks, i
 // Right-hand sides: ny columns, either Y itself (LIFTED false; ny = n <= 8)
 // or, for the lifted operator, the ny = D features psi(Y_t, U_t) (the input
 // held over the step), lifted on the fly like the rows of Psi.
-template <bool LIFTED>
+// PB: column blocks of Psi, as many as its features fill (one, two or four).  With four for every
+// basis the products of zeros bound small ones: 3 features of [x; u], 2,000,000
+// rows, 620 us and the lifted operator 792 (592 both by scalar FMAs), now 302 and
+// 248; the balance bot's 21 557 and 705, now 385 and 311.
+template <bool LIFTED, int PB>
 struct GramShape {
-  static constexpr int RB = LIFTED ? 4 : 1;               // right-hand-side blocks
-  static constexpr int MW = LIFTED ? 8 : 4;               // waves on the products
+  static constexpr int RB = LIFTED ? PB : 1;              // right-hand-side blocks
+  static constexpr int kGram = PB * (PB + 1) / 2;         // blocks on and above the diagonal
+  static constexpr int kTiles = kGram + PB * RB;
+  static constexpr int MW = PB == 1 ? 2 : LIFTED ? 8 : 4;  // waves on the products
   static constexpr int LW = LIFTED ? 4 : 2;               // waves lifting
-  static constexpr int kTiles = 10 + kPsiBlocks * RB;     // 10 on and above the diagonal
   static constexpr int kPerWave = (kTiles + MW - 1) / MW;
-  static constexpr int kStride = 16 * (kPsiBlocks + RB) + 1;
+  static constexpr int kStride = 16 * (PB + RB) + 1;
   static constexpr int kThreads = 64 * (MW + LW);
 };
 
-template <bool LIFTED>
-__global__ void __launch_bounds__(GramShape<LIFTED>::kThreads)
+template <bool LIFTED, int PB>
+__global__ void __launch_bounds__((GramShape<LIFTED, PB>::kThreads))
 gram_kernel(mpmi_system sys, int D, int ny, const double* __restrict__ X, const double* __restrict__ U,
             const double* __restrict__ Y, long long T, double* __restrict__ part) {
-  using GS = GramShape<LIFTED>;
+  using GS = GramShape<LIFTED, PB>;
   __shared__ __attribute__((aligned(16))) double Z[2][kFitRows][GS::kStride];
   const int n = sys.n_state, m = sys.n_input;
   const int C = D + ny;
@@ -152,8 +157,8 @@ gram_kernel(mpmi_system sys, int D, int ny, const double* __restrict__ X, const 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool lifter = wave < GS::LW;
   const int mw = wave - GS::LW;
-  // This wave's blocks: number q is (I, J), J < 4 a feature block (I <= J, in
-  // column order), J >= 4 right-hand-side block J - 4.
+  // This wave's blocks: number q is (I, J), J < PB a feature block (I <= J, in
+  // column order), J >= PB right-hand-side block J - PB.
   f64x4_t acc[GS::kPerWave];
   int bi[GS::kPerWave], bj[GS::kPerWave];
   bool on[GS::kPerWave];
@@ -163,12 +168,12 @@ gram_kernel(mpmi_system sys, int D, int ny, const double* __restrict__ X, const 
     // between the products and their LDS reads.
     const int q0 = mw + GS::MW * k, q = q0 < 0 || q0 >= GS::kTiles ? 0 : q0;
     int i, j;
-    if (q < 10) {
+    if (q < GS::kGram) {
       j = q < 1 ? 0 : (q < 3 ? 1 : (q < 6 ? 2 : 3));
       i = q - j * (j + 1) / 2;
     } else {
-      i = (q - 10) & 3;
-      j = 4 + ((q - 10) >> 2);
+      i = (q - GS::kGram) % PB;
+      j = PB + (q - GS::kGram) / PB;
     }
     bi[k] = i;
     bj[k] = j;
@@ -181,14 +186,14 @@ gram_kernel(mpmi_system sys, int D, int ny, const double* __restrict__ X, const 
   auto lift_tile = [&](long long k, int buf) {
     const long long r = (blockIdx.x + k * gridDim.x) * kFitRows + lane;
     double* z = Z[buf][lane];
-    double* y = z + 16 * kPsiBlocks;
+    double* y = z + 16 * PB;
     if (r >= T) {
       for (int q = wave; q < GS::kStride - 1; q += GS::LW) z[q] = 0.0;
       return;
     }
     if (wave == 0) {
       lift_row<0>(sys, X + r * n, U + r * m, z);
-      for (int q = D; q < 16 * kPsiBlocks; ++q) z[q] = 0.0;
+      for (int q = D; q < 16 * PB; ++q) z[q] = 0.0;
       if constexpr (!LIFTED) {
         for (int q = 0; q < ny; ++q) y[q] = Y[r * n + q];
         for (int q = ny; q < 16 * GS::RB; ++q) y[q] = 0.0;
@@ -242,8 +247,8 @@ gram_kernel(mpmi_system sys, int D, int ny, const double* __restrict__ X, const 
 #pragma unroll
   for (int q = 0; q < GS::kPerWave; ++q) {
     if (!on[q]) continue;
-    const int col = 16 * (bj[q] & 3) + (lane & 15);
-    const bool rhs = bj[q] >= 4;
+    const bool rhs = bj[q] >= PB;
+    const int col = 16 * (bj[q] - (rhs ? PB : 0)) + (lane & 15);
     if (col >= (rhs ? ny : D)) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -637,7 +642,7 @@ size_t fit_workspace_bytes() { return (size_t)(kFitBlocks + 1) * MPMI_MAX_DIM * 
 // solved eight columns at a time).  The Gram pass is bound by the lift of a
 // tile (two waves, 3.7 us against 2.3 us of products); 256 workgroups fix the
 // order of the sums.
-template <bool LIFTED>
+template <bool LIFTED, int PB>
 static hipError_t fit_columns(const mpmi_system& sys, int dim, int ny, const double* X, const double* U,
                               const double* Y, int64_t T, double ridge, double* K_out, void* work, FitInfo* info,
                               hipStream_t st) {
@@ -646,19 +651,21 @@ static hipError_t fit_columns(const mpmi_system& sys, int dim, int ny, const dou
   const int nparts = (int)(ntiles < kFitBlocks ? ntiles : kFitBlocks);
   double* part = (double*)work;
   double* tot = part + (size_t)kFitBlocks * MPMI_MAX_DIM * kFitColsMax;
-  gram_kernel<LIFTED><<<nparts, GramShape<LIFTED>::kThreads, 0, st>>>(sys, dim, ny, X, U, Y, (long long)T, part);
+  using GS = GramShape<LIFTED, PB>;
+  gram_kernel<LIFTED, PB><<<nparts, GS::kThreads, 0, st>>>(sys, dim, ny, X, U, Y, (long long)T, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   reduce_kernel<<<(E + kReduceElems - 1) / kReduceElems, kReduceElems * kReduceWays, 0, st>>>(nparts, E, part, tot);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  solve_kernel<GramShape<LIFTED>::RB><<<2, kFitThreads, 0, st>>>(ny, dim, (long long)T, ridge, tot, K_out, info);
+  solve_kernel<GS::RB><<<2, kFitThreads, 0, st>>>(ny, dim, (long long)T, ridge, tot, K_out, info);
   return hipGetLastError();
 }
 
 hipError_t launch_fit(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
                       int64_t T, double ridge, double* K_out, void* work, FitInfo* info, hipStream_t st) {
-  return fit_columns<false>(sys, dim, sys.n_state, X, U, Y, T, ridge, K_out, work, info, st);
+  auto fit = dim <= 16 ? fit_columns<false, 1> : dim <= 32 ? fit_columns<false, 2> : fit_columns<false, kPsiBlocks>;
+  return fit(sys, dim, sys.n_state, X, U, Y, T, ridge, K_out, work, info, st);
 }
 
 // The lifted operator K (dim x dim, targets psi(Y_t, U_t)): the same scaled
@@ -667,7 +674,8 @@ hipError_t launch_fit(const mpmi_system& sys, int dim, const double* X, const do
 // forming the Gram matrix and its factor again.
 hipError_t launch_fit_lifted(const mpmi_system& sys, int dim, const double* X, const double* U, const double* Y,
                              int64_t T, double ridge, double* K_out, void* work, FitInfo* info, hipStream_t st) {
-  return fit_columns<true>(sys, dim, dim, X, U, Y, T, ridge, K_out, work, info, st);
+  auto fit = dim <= 16 ? fit_columns<true, 1> : dim <= 32 ? fit_columns<true, 2> : fit_columns<true, kPsiBlocks>;
+  return fit(sys, dim, dim, X, U, Y, T, ridge, K_out, work, info, st);
 }
 
 }  // namespace mpmi
