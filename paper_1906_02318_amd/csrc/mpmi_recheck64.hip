@@ -836,22 +836,38 @@ __device__ __forceinline__ int evaluate64_row(const ModelDev* __restrict__ md, c
 // kernel has no more: three-input car, 64 features, 25 steps, 32,768: 299 and
 // 391; 49,152: 399 and 605; 262,144: 1671 and 2368 (by itself, three waves per
 // SIMD, the lane form takes 485 and 1762).
+//
+// With process noise every lane of a row forms its draw, four times the lane
+// form's logarithms and square roots, so rows lose earlier, and beside them in one
+// kernel (249 VGPRs) the lane form was the slower itself (153 alone).  Each has a
+// kernel of its own there; the second launch, of ticks that may keep more than
+// kRowEntriesNoisy, costs 2 us.  Balance bot, 50 steps, every candidate kept, in one
+// kernel and in two (before rows): 8,192 193 and 159 us (352), 24,576 328 and 307
+// (369), 32,768 442 and 371 (368), 40,001 538 and 377 (374), 131,072 1046 and 857 (867).
 constexpr int kRowEntriesDescribed = 32768;
-template <int DEG, int KD, bool NOISE>
+constexpr int kRowEntriesNoisy = 24576;  // three turns of two waves per SIMD
+enum class Form { kByLength, kRows, kLanes };
+template <int DEG, int KD, bool NOISE, Form FORM = Form::kByLength>
 __global__ void __launch_bounds__(kR64Block)
 recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const float* __restrict__ x_t,
                  const float* __restrict__ u_user, const float* __restrict__ cand, Slot* __restrict__ slot,
                  mpmi_selection* __restrict__ out, int16_t* __restrict__ fv_out, RecheckList* __restrict__ rl,
                  int capacity, const mpmi_selection* __restrict__ gate) {
   __shared__ double sK[MPMI_MAX_DIM * 8];
-  __shared__ double sAt[MPMI_MAX_ATOMS * kR64Block];
+  __shared__ double sAt[FORM == Form::kRows ? 4 * kRowLds : MPMI_MAX_ATOMS * kR64Block];
   static_assert(4 * kRowLds <= MPMI_MAX_ATOMS * kR64Block, "a wave's rows");
   // Gated tick (a fallback after a proposal tick): nothing ran, nothing to finalise.
   if (gate && gate->status == MPMI_OK) return;
   const unsigned int kn = rl->n_keep;
   const int n_keep = (int)(kn < (unsigned int)capacity ? kn : (unsigned int)capacity);
+  if constexpr (FORM == Form::kLanes) {  // after the rows' launch, which empties a list it has taken
+    if (n_keep <= kRowEntriesNoisy) return;
+  }
   if (recheck_nothing_kept(md, gp, H, u_user, cand, slot, out, rl, n_keep)) return;
-  const bool rows = KD > 32 || n_keep <= kRowEntriesDescribed;
+  if constexpr (FORM == Form::kRows && KD <= 32) {
+    if (n_keep > kRowEntriesNoisy) return;
+  }
+  const bool rows = FORM == Form::kRows || (FORM == Form::kByLength && n_keep <= kRowEntriesDescribed);
   const int per = rows ? kR64Block / 16 : kR64Block;  // candidates per workgroup pass
   const int parts = min((int)gridDim.x, (n_keep + per - 1) / per);
   if ((int)blockIdx.x >= parts) return;  // uniform
@@ -869,7 +885,7 @@ recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const flo
     kf = b < kf ? b : kf;
     n_safe += (safe && c > 0) ? 1u : 0u;
   };
-  if (rows) {
+  if constexpr (FORM != Form::kLanes) if (rows) {
     for (int q0 = blockIdx.x * per; q0 < n_keep; q0 += parts * per) {  // uniform
       const int q = q0 + (lane >> 4);
       const bool valid = q < n_keep;
@@ -878,7 +894,8 @@ recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const flo
                                                     sAt + (lane >> 4) * kRowLds);
       if (valid && (lane & 15) == 0) publish(c, fv);
     }
-  } else {
+  }
+  if constexpr (FORM != Form::kRows) if (!rows) {
     const double* Kg = &md->m64.K[0][0];
     for (int e = lane; e < MPMI_MAX_DIM * 8; e += kR64Block) sK[e] = Kg[e];
     __syncthreads();
@@ -892,7 +909,8 @@ recheck64_kernel(const ModelDev* __restrict__ md, GenParams gp, int H, const flo
 
 template <int DEG, bool NOISE>
 static auto described_kernel(bool wide) {  // wide: more than 32 features
-  return wide ? recheck64_kernel<DEG, 64, NOISE> : recheck64_kernel<DEG, 32, NOISE>;
+  return wide ? recheck64_kernel<DEG, 64, NOISE, Form::kRows>
+              : recheck64_kernel<DEG, 32, NOISE, NOISE ? Form::kRows : Form::kByLength>;
 }
 
 // Race car: four kept candidates to a wave (evaluate64_rc16), or eight
@@ -1006,6 +1024,11 @@ hipError_t launch_recheck64(const mpmi_system& sys, const void* model, const mpm
                 : noisy        ? described_kernel<kMaxHarm, true>(wide)
                                : described_kernel<kMaxHarm, false>(wide);
     kern<<<grid * 4, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl, capacity, gate);
+    if (noisy && !wide && (long long)d.n_cand + 1 > kRowEntriesNoisy) {
+      auto lanes = small ? recheck64_kernel<kSmallTrackDeg, 32, true, Form::kLanes>
+                         : recheck64_kernel<kMaxHarm, 32, true, Form::kLanes>;
+      lanes<<<grid, kR64Block, 0, st>>>(md, gp, d.horizon, x_t, u_user, cand, sl, out, fv, rl, capacity, gate);
+    }
   }
   return hipGetLastError();
 }
